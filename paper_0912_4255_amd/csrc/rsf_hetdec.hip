@@ -5,9 +5,9 @@
 // so the filter runs with complex taps g[i] = h[i] exp(-2 pi i f_h (c - i) dt)
 // on the real series and each output takes one FP64 phase factor.
 //
-// Two forms: for D = 64 and K = 8, 12 or 16 a product on the FP32 matrix
-// cores (rsf_hetdec_mfma_k, below); for every other D and K a direct sum
-// (rsf_hetdec_k): one workgroup per 64 outputs, the raw samples its outputs
+// Two forms: filters of at least 4 D + 1 taps whose window fits LDS run as a
+// product on the FP32 matrix cores (rsf_hetdec_mfma_k, below); the others a
+// direct sum (rsf_hetdec_k): one workgroup per 64 outputs, the raw samples its outputs
 // touch and the taps in LDS, each wave computing four outputs at a time with
 // its lanes striding over the taps (consecutive lanes read consecutive
 // samples and taps), then summing across the wave.
@@ -81,139 +81,321 @@ __global__ __launch_bounds__(kHdThreads) void rsf_hetdec_k(HetdecArgs a) {
     }
 }
 
-// Matrix-core form for D = 64.  With raw rows X[q][p] = x[64 q + p], output j
-// is sum_i g[i] x[64 j + c - i], c = 64 K; writing the raw index as 64 q + p
-// gives i = 64 (j - q + K) - p, so with m = j - q
-//   y_j = sum_{m=-K+1}^{K} Z[j - m][m] + g[0] X[j + K][0],
-//   Z[q][m] = sum_p X[q][p] G[m][p],  G[m][p] = g[64 (m + K) - p]
-// (m = -K leaves only the tap g[0]).  Z is a real product of the rows
-// (64 columns) with the 64 x 4K matrix B[p][c] = Re G[m][p] (c = m + K - 1
-// < 2K) or Im G[m][p] (c = m + 3K - 1): FP32 MFMA 16x16x4 tiles, B held in
-// registers, A read from rows staged in LDS.  A block is 256 rows: its
-// J = 256 - 2K outputs and a halo of K rows on each side.  Persistent
-// workgroups (one per CU) walk the blocks with two row buffers: the next
-// block's rows arrive by DMA (global -> LDS) while the current block's Z is
-// computed in place of its rows (each wave owns one 16-row tile), then one
-// thread per output adds the 2K diagonal terms and applies the output phase.
+// Matrix-core form.  Output j = 8 J + n (n < 8) reads
+// x[8 D J + n D + c - i] g[i], so with row J's window starting at its sample
+// 8 D J + c - (L - 1), output (J, n) is the product of that window with the
+// taps shifted by n D:
+//   y_{8J+n} = sum_kk X[8 D J + kk] G[kk][n],  G[kk][n] = g[(L - 1) + n D - kk]
+// (zero outside the filter), kk < Kd = L + 7 D.  The 16 columns (8 outputs, real
+// and imaginary parts) and 16 rows J are one FP32 MFMA 16x16x4 tile; the
+// columns' zero taps cost 7 / (2 K) more products than the direct sum.  The
+// length Kd is split over WK waves, each holding its slice of G in registers
+// for the whole launch; the 16 / WK row tiles of a block are the other way the
+// waves divide.  Partial tiles are added through LDS (a split sum of WK parts).
+//
+// Persistent workgroups walk consecutive blocks (the overlap of neighbouring
+// windows stays in their caches).  One barrier per block: after it, the next
+// block's window comes by DMA into the other buffer, the last block's partial
+// tiles are added and written, and this block's products run.  The buffers are
+// LDS arrays of their own, so no LDS read of one waits for the DMA into the
+// other.  Rows start 8 D samples apart, on the same banks when D is even; then
+// four floats between the window's chunks of 8 D samples move the rows' 16-byte
+// reads to different banks (an odd D has at most two rows on a bank).  Windows
+// of which two do not fit LDS run with one buffer and no prefetch.
+//
+// The columns' zero taps would spread a sample that is not finite over its
+// row: an output whose sum is not finite is summed again directly.
+//
+// What bounds it: the FP32 matrix rate (4 flops per tap and output, 153.8
+// TFLOP/s measured by a large product).  Ten days at 256 Hz, D = 64, K = 16:
+// 277 us for the products alone (82 % of that rate with the zero taps), 201 us
+// for the samples alone (5 TB/s), about 400 us for both together; the product
+// form for D = 64 alone that this replaces (rows of 64 samples, one output tap
+// phase per column, a diagonal sum through LDS) took 404 us.  One day at 1 kHz,
+// D = 100, K = 16: 177 us against 1530 us for the direct sum.  Vector
+// instructions hold up FP32 products: with the samples staged through registers
+// (237 vector instructions per wave and block, 17 of them products) the D = 64
+// case took 546 us.  A third window buffer changed nothing.
 namespace {
-constexpr int kMmRows = 256;     // raw rows per block, halo included
-constexpr int kMmStride = 66;    // LDS row stride in floats: A reads, Z writes and diagonal reads at most 2-way
-constexpr int kMmThreads = 1024;  // 4 waves per SIMD
-constexpr int kMmBuf = kMmRows * kMmStride;
+constexpr int kMmThreads = 1024;  // 16 waves, 4 per SIMD
+constexpr int kMmWaves = kMmThreads / 64;
+// floats of one of NB window buffers (the partial tiles have the other 32 KiB of LDS)
+constexpr int mm_buf(int NB) { return 32768 / NB; }
 typedef float mm_v4f __attribute__((ext_vector_type(4)));
+
+// The split of one plan: WK waves along the taps, NG groups of 16 taps each.
+struct MmShape {
+    int WK = 0, NG = 0, NB = 0;  // NB window buffers
+};
+
+// NG is compiled for these values, 18 and 20 for one buffer only
+constexpr int kMmGroups[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 18, 20};
+
+int mm_pad(int D) { return (D & 1) ? 0 : 4; }
+
+MmShape mm_shape_of(int L, int D, int WK) {
+    MmShape m;
+    const int Kd = L + 7 * D, WM = kMmWaves / WK;
+    const int need = (Kd + 16 * WK - 1) / (16 * WK);
+    int NG = 0;
+    for (int g : kMmGroups)
+        if (g >= need) {
+            NG = g;
+            break;
+        }
+    if (!NG) return m;
+    // the last row reads KR taps from its start; its window has Kd of them in whole chunks of 8 D
+    const int KR = 16 * NG * WK;
+    const int64_t stride = 8 * D + mm_pad(D), rows = 16 * WM - 1;
+    const int64_t floats = std::max((rows + (Kd + 8 * D - 1) / (8 * D)) * stride,
+                                    rows * stride + KR + (int64_t)(KR / (8 * D)) * mm_pad(D) + 16);
+    const int NB = floats <= mm_buf(2) ? 2 : floats <= mm_buf(1) ? 1 : 0;
+    if (!NB || (NB == 1 ? WK != kMmWaves || NG < 8 : NG > 16)) return m;
+    m.NB = NB;
+    m.WK = WK;
+    m.NG = NG;
+    return m;
+}
+
+// The form a plan of L taps takes for n_out outputs (WK = 0: the direct sum).
+// Filters under 4 D + 1 taps would meet more zero taps than their own.
+MmShape mm_shape(int L, int D, int64_t n_out, int n_cu) {
+    MmShape best;
+    if (D < 2 || L < 4 * D + 1) return best;
+    for (int WK : {4, 8, 16}) {
+        const MmShape m = mm_shape_of(L, D, WK);
+        if (!m.WK || (best.WK && m.NB < 2)) continue;
+        if (best.WK) {
+            // fewer row tiles per block only where larger blocks leave compute units idle
+            const int64_t per_block = 128 * (kMmWaves / best.WK);
+            if ((n_out + per_block - 1) / per_block >= 2 * (int64_t)n_cu) break;
+        }
+        best = m;
+    }
+    return best;
+}
 }  // namespace
 
-template <int K>
-__global__ __launch_bounds__(kMmThreads) void rsf_hetdec_mfma_k(HetdecArgs a) {
-    constexpr int NTL = K / 4;               // 16-column tiles of the 4K columns
-    constexpr int J = kMmRows - 2 * K;       // outputs per block
-    extern __shared__ float xz[];             // two buffers [kMmRows][kMmStride]: raw rows, then Z
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t n_blk = (a.n_out + J - 1) / J;
-    // B operand of k step s and column tile n: lane holds B[4 s + lane / 16][16 n + lane % 16]
-    float bop[16][NTL];
+template <int WK, int NG, int NB>
+__global__ __launch_bounds__(kMmThreads) void rsf_hetdec_mfma_k(HetdecArgs a, int pad, unsigned inv_chunk, bool wide,
+                                                                 int64_t n_blk) {
+    constexpr int WM = kMmWaves / WK;
+    constexpr int NO = 128 * WM;  // outputs per block
+    __shared__ __align__(16) float buf0[mm_buf(NB)];
+    __shared__ __align__(16) float buf1[NB > 1 ? mm_buf(NB) : 4];
+    __shared__ __align__(16) float red[2][kMmWaves][256];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kw = wave % WK, mt = wave / WK;
+    const int D = a.D, L = a.L, chunk = 8 * D, stride = chunk + pad;
+    const int J = lane & 15, q = lane >> 4;
+    // This wave's group g of 16 taps is kk = 16 (kw + WK g): the waves take
+    // groups in turn, so no partial sum holds the filter's main lobe alone, and
+    // the four taps of a lane have an accumulator each: chains as short as the
+    // direct sum's.  The error against 64 bits is the direct sum's (1.5e-7
+    // relative at D = 100, K = 16); with contiguous slices and two accumulators
+    // it was 2.2e-7 at 158 us.
+    // B operand: lane holds G[16 (kw + WK g) + 4 q + t][lane % 16]; taps
+    // outside the filter are outside the buffer and read zero
+    float bop[NG][4];
+    {
+        const __amdgpu_buffer_rsrc_t taps =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(a.g), 0, 8 * L, 0x00027000);
+        const int at = 8 * ((L - 1) + (J >> 1) * D - (16 * kw + 4 * q)) + 4 * (J & 1);
 #pragma unroll
-    for (int s = 0; s < 16; ++s) {
-        const int pp = 4 * s + (lane >> 4);
+        for (int g = 0; g < NG; ++g)
 #pragma unroll
-        for (int n = 0; n < NTL; ++n) {
-            const int col = 16 * n + (lane & 15);
-            const int mk = col < 2 * K ? col : col - 2 * K;   // m + K - 1
-            const float2 gv = a.g[64 * (mk + 1) - pp];
-            bop[s][n] = col < 2 * K ? gv.x : gv.y;
-        }
+            for (int t = 0; t < 4; ++t)
+                bop[g][t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(taps, at - 8 * (16 * WK * g + t), 0, 0));
     }
-    const float2 g0 = a.g[0];
-    // rows of block b by DMA, one row of 64 samples per wave instruction;
-    // samples outside the series are zero
-    auto stage = [&](int64_t b, float* buf) {
-        const int64_t r0 = b * J - K;
-        for (int row = wave; row < kMmRows; row += kMmThreads / 64) {
-            const int64_t m = (r0 + row) * 64 + lane;
-            if (m >= 0 && m < a.n_raw)
-                __builtin_amdgcn_global_load_lds((const void*)(a.x + m),
-                                                 (__attribute__((address_space(3))) void*)(buf + row * kMmStride), 4, 0,
-                                                 0);
-            else
-                buf[row * kMmStride + lane] = 0.f;
-        }
-    };
-    int64_t b = blockIdx.x;
-    if (b < n_blk) stage(b, xz);
-    for (int it = 0; b < n_blk; ++it, b += gridDim.x) {
-        float* buf = xz + (it & 1) * kMmBuf;
-        // this thread's DMA for block b (and its earlier stores) have landed;
-        // after the barrier, everyone's, and the other buffer's last block is
-        // fully consumed
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (b + gridDim.x < n_blk) stage(b + gridDim.x, xz + ((it + 1) & 1) * kMmBuf);
-        // X[j + K][0], the sample of the tap g[0], from global memory (the rows
-        // in LDS are overwritten by Z below)
-        const int64_t m0 = (b * J + tid + K) * 64;
-        const float x0 = (tid < J && m0 < a.n_raw) ? a.x[m0] : 0.f;
-        for (int rt = wave; rt < kMmRows / 16; rt += kMmThreads / 64) {
-            mm_v4f acc[NTL];
-#pragma unroll
-            for (int n = 0; n < NTL; ++n) acc[n] = mm_v4f{0.f, 0.f, 0.f, 0.f};
-            // A operand: lane holds X[16 rt + lane % 16][4 s + lane / 16]
-            const float* arow = buf + (16 * rt + (lane & 15)) * kMmStride + (lane >> 4);
-#pragma unroll
-            for (int s = 0; s < 16; ++s) {
-                const float av = arow[4 * s];
-#pragma unroll
-                for (int n = 0; n < NTL; ++n)
-                    acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bop[s][n], acc[n], 0, 0, 0);
+
+    // consecutive blocks per workgroup
+    const int64_t per = n_blk / gridDim.x, rest = n_blk - per * gridDim.x;
+    const int64_t b0 = per * blockIdx.x + min((int64_t)blockIdx.x, rest);
+    const int n_it = (int)(per + ((int64_t)blockIdx.x < rest ? 1 : 0));
+
+    // The window of block b: chunks of 8 D samples (all that the rows' Kd taps
+    // reach), a piece of 64 lanes per wave instruction, 16 bytes a lane where
+    // every window starts on 16 bytes; samples outside the series are zero.
+    // The addresses are a scalar base and the lane's offset, and the waves that
+    // issue go first (priority): vector instructions wait behind the products of
+    // the waves that are done with it.
+    const int n_chunks = 16 * WM - 1 + (L + 7 * D + chunk - 1) / chunk;
+    // what the last rows' zero taps read past the window is zero, once
+    for (int i = n_chunks * stride + tid; i < mm_buf(NB); i += kMmThreads) {
+        buf0[i] = 0.f;
+        if (NB > 1) buf1[i] = 0.f;
+    }
+    const int piece = wide ? 256 : 64, pieces = (chunk + piece - 1) / piece;
+    auto stage = [&](int64_t b, float* w) {
+        const int64_t m0 = b * NO * (int64_t)D + a.c - (L - 1);  // raw sample of the window's first
+        __builtin_amdgcn_s_setprio(3);
+        if (m0 >= 0 && m0 + (int64_t)n_chunks * chunk <= a.n_raw) {
+            const float* x0 = a.x + m0;
+            int c = wave / pieces, p = wave - c * pieces;
+            while (c < n_chunks) {
+                const float* from = x0 + c * chunk + p * piece;
+                float* to = w + c * stride + p * piece;
+                if (wide) {
+                    if (4 * lane < chunk - p * piece)
+                        __builtin_amdgcn_global_load_lds((const void*)(from + 4 * lane),
+                                                         (__attribute__((address_space(3))) void*)to, 16, 0, 0);
+                } else {
+                    if (lane < chunk - p * piece)
+                        __builtin_amdgcn_global_load_lds((const void*)(from + lane),
+                                                         (__attribute__((address_space(3))) void*)to, 4, 0, 0);
+                }
+                p += kMmWaves;
+                while (p >= pieces) {
+                    p -= pieces;
+                    ++c;
+                }
             }
-            // D layout: lane holds Z[16 rt + 4 (lane / 16) + v][16 n + lane % 16];
-            // the tile's rows were read only by this wave, above
-#pragma unroll
-            for (int n = 0; n < NTL; ++n)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    buf[(16 * rt + 4 * (lane >> 4) + v) * kMmStride + 16 * n + (lane & 15)] = acc[n][v];
+        } else {
+            for (int i = tid; i < n_chunks * chunk; i += kMmThreads) {
+                const int64_t m = m0 + i;
+                const int c = i / chunk;
+                w[i + c * pad] = (m >= 0 && m < a.n_raw) ? a.x[m] : 0.f;
+            }
         }
-        __syncthreads();
-        const int64_t j = b * J + tid;
-        if (tid < J && j < a.n_out) {
-            float re = g0.x * x0, im = g0.y * x0;
+        __builtin_amdgcn_s_setprio(0);
+    };
+
+    // adds the WK partial tiles of block b and writes its outputs: thread
+    // e of a tile has element (row 4 (l / 16) + v, column l % 16), l = e / 4, v = e % 4
+    auto finish = [&](int64_t b, const float (*part)[256]) {
+        if (tid < 256 * WM) {  // whole waves
+            const int tile = tid >> 8, e = tid & 255, l = e >> 2, v = e & 3;
+            float t[WK];
 #pragma unroll
-            for (int mk = 0; mk < 2 * K; ++mk) {
-                const float* z = buf + (tid + 2 * K - 1 - mk) * kMmStride;  // row of q = j - m, m = mk - K + 1
-                re += z[mk];
-                im += z[2 * K + mk];
+            for (int w = 0; w < WK; ++w) t[w] = part[tile * WK + w][e];
+#pragma unroll
+            for (int h = WK / 2; h > 0; h /= 2)
+#pragma unroll
+                for (int w = 0; w < h; ++w) t[w] += t[w + h];
+            float s = t[0];
+            float o = __shfl_xor(s, 4);  // the other part of the same output
+            const bool im = l & 1;
+            const int64_t j = b * NO + 128 * tile + 8 * (4 * (l >> 4) + v) + ((l & 15) >> 1);
+            if (j >= a.n_out) return;
+            if (!(fabsf(s) <= 3.402823466e38f && fabsf(o) <= 3.402823466e38f)) {
+                s = o = 0.f;
+                for (int i = 0; i < L; ++i) {
+                    const int64_t m = j * D + a.c - i;
+                    if (m < 0 || m >= a.n_raw) continue;
+                    const float2 t = a.g[i];
+                    s += (im ? t.y : t.x) * a.x[m];
+                    o += (im ? t.x : t.y) * a.x[m];
+                }
             }
             const double cyc = a.cyc_per_out * (double)j;
             float sn, cs;
             sincospif(-2.0f * (float)(cyc - rint(cyc)), &sn, &cs);
-            a.out[j] = make_float2(re * cs - im * sn, re * sn + im * cs);
+            reinterpret_cast<float*>(a.out)[2 * j + (im ? 1 : 0)] = im ? o * sn + s * cs : s * cs - o * sn;
+        }
+    };
+
+    // this block's products into its wave's partial tile
+    auto multiply = [&](const float* w, float (*part)[256]) {
+        const float* row = w + (16 * mt + J) * stride + 4 * q;
+        mm_v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0, acc2 = acc0, acc3 = acc0;
+        // with padding 8 D is a multiple of 16, so a group of 16 taps lies in one chunk
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const unsigned kk = 16 * (kw + WK * g);
+            const float4 x = *reinterpret_cast<const float4*>(row + kk + pad * (int)(((uint64_t)kk * inv_chunk) >> 32));
+            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, bop[g][0], acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, bop[g][1], acc1, 0, 0, 0);
+            acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, bop[g][2], acc2, 0, 0, 0);
+            acc3 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, bop[g][3], acc3, 0, 0, 0);
+        }
+        // D layout: lane holds rows 4 (lane / 16) + v, column lane % 16
+        *reinterpret_cast<float4*>(part[mt * WK + kw] + 4 * lane) =
+            make_float4((acc0[0] + acc1[0]) + (acc2[0] + acc3[0]), (acc0[1] + acc1[1]) + (acc2[1] + acc3[1]),
+                        (acc0[2] + acc1[2]) + (acc2[2] + acc3[2]), (acc0[3] + acc1[3]) + (acc2[3] + acc3[3]));
+    };
+
+    if constexpr (NB > 1) {
+        auto step = [&](int it, const float* w, float* next, float (*part)[256], const float (*last)[256]) {
+            __builtin_amdgcn_s_waitcnt(0);  // this wave's DMA for the block has landed
+            __syncthreads();
+            if (it + 1 < n_it) stage(b0 + it + 1, next);
+            if (it > 0) finish(b0 + it - 1, last);
+            multiply(w, part);
+        };
+        if (n_it > 0) stage(b0, buf0);
+        for (int it = 0; it < n_it; it += 2) {
+            step(it, buf0, buf1, red[0], red[1]);
+            if (it + 1 < n_it) step(it + 1, buf1, buf0, red[1], red[0]);
+        }
+    } else {
+        for (int it = 0; it < n_it; ++it) {
+            __syncthreads();
+            stage(b0 + it, buf0);
+            if (it > 0) finish(b0 + it - 1, red[(it - 1) & 1]);
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            multiply(buf0, red[it & 1]);
         }
     }
+    __syncthreads();
+    if (n_it > 0) finish(b0 + n_it - 1, red[(n_it - 1) & 1]);
 }
 
 namespace {
-bool hetdec_mfma_form(int L, int D) {
-    const int K = D > 0 ? (L - 1) / (2 * D) : 0;
-    return D == 64 && (K == 8 || K == 12 || K == 16);
+typedef void (*MmFn)(HetdecArgs, int, unsigned, bool, int64_t);
+
+template <int WK>
+MmFn mm_fn(int NG) {
+    switch (NG) {
+        case 1: return rsf_hetdec_mfma_k<WK, 1, 2>;
+        case 2: return rsf_hetdec_mfma_k<WK, 2, 2>;
+        case 3: return rsf_hetdec_mfma_k<WK, 3, 2>;
+        case 4: return rsf_hetdec_mfma_k<WK, 4, 2>;
+        case 5: return rsf_hetdec_mfma_k<WK, 5, 2>;
+        case 6: return rsf_hetdec_mfma_k<WK, 6, 2>;
+        case 8: return rsf_hetdec_mfma_k<WK, 8, 2>;
+        case 10: return rsf_hetdec_mfma_k<WK, 10, 2>;
+        case 12: return rsf_hetdec_mfma_k<WK, 12, 2>;
+        case 14: return rsf_hetdec_mfma_k<WK, 14, 2>;
+        case 16: return rsf_hetdec_mfma_k<WK, 16, 2>;
+        default: return nullptr;
+    }
+}
+
+MmFn mm_kernel(const MmShape& m) {
+    if (m.NB == 1) {
+        switch (m.NG) {
+            case 8: return rsf_hetdec_mfma_k<16, 8, 1>;
+            case 10: return rsf_hetdec_mfma_k<16, 10, 1>;
+            case 12: return rsf_hetdec_mfma_k<16, 12, 1>;
+            case 14: return rsf_hetdec_mfma_k<16, 14, 1>;
+            case 16: return rsf_hetdec_mfma_k<16, 16, 1>;
+            case 18: return rsf_hetdec_mfma_k<16, 18, 1>;
+            case 20: return rsf_hetdec_mfma_k<16, 20, 1>;
+            default: return nullptr;
+        }
+    }
+    return m.WK == 4 ? mm_fn<4>(m.NG) : m.WK == 8 ? mm_fn<8>(m.NG) : m.WK == 16 ? mm_fn<16>(m.NG) : nullptr;
 }
 }  // namespace
 
+// The direct sum's LDS: what a plan's taps and decimation may need at most.
 size_t hetdec_lds(int L, int D) {
-    if (hetdec_mfma_form(L, D)) return (size_t)2 * kMmBuf * sizeof(float);
     return (size_t)2 * L * sizeof(float) + (size_t)((kHdOut - 1) * D + L) * sizeof(float);
 }
 
 hipError_t launch_hetdec(const HetdecArgs& a, int n_cu, hipStream_t s) {
-    if (hetdec_mfma_form(a.L, a.D)) {
-        const int K = a.c / a.D;
-        const size_t lds = hetdec_lds(a.L, a.D);
-        const int64_t n_blk = (a.n_out + (kMmRows - 2 * K) - 1) / (kMmRows - 2 * K);
+    const MmShape m = mm_shape(a.L, a.D, a.n_out, n_cu);
+    if (MmFn fn = mm_kernel(m)) {
+        const int64_t no = 128 * (kMmWaves / m.WK);
+        const int64_t n_blk = (a.n_out + no - 1) / no;
         const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n_blk, n_cu));
-        switch (K) {
-            case 8: hipLaunchKernelGGL(rsf_hetdec_mfma_k<8>, dim3(grid), dim3(kMmThreads), lds, s, a); break;
-            case 12: hipLaunchKernelGGL(rsf_hetdec_mfma_k<12>, dim3(grid), dim3(kMmThreads), lds, s, a); break;
-            default: hipLaunchKernelGGL(rsf_hetdec_mfma_k<16>, dim3(grid), dim3(kMmThreads), lds, s, a); break;
-        }
+        // windows start at samples 128 k D - K D
+        const bool wide = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && a.c % 4 == 0;
+        // kk / (8 D) for kk < 2^16 by the reciprocal rounded up
+        const unsigned inv = (unsigned)(((1ull << 32) + 8ull * a.D - 1) / (8ull * a.D));
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(kMmThreads), 0, s, a, mm_pad(a.D), inv, wide, n_blk);
         return hipGetLastError();
     }
     const unsigned grid = (unsigned)((a.n_out + kHdOut - 1) / kHdOut);
@@ -221,18 +403,13 @@ hipError_t launch_hetdec(const HetdecArgs& a, int n_cu, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Grants the direct sum's LDS, which only grows (the matrix-core form's is static).
 hipError_t hetdec_set_lds_limit(size_t bytes) {
-    static size_t granted = 0;  // only grows
+    static size_t granted = 0;
     if (bytes <= granted) return hipSuccess;
-    const void* fns[] = {(const void*)rsf_hetdec_k, (const void*)rsf_hetdec_mfma_k<8>,
-                         (const void*)rsf_hetdec_mfma_k<12>, (const void*)rsf_hetdec_mfma_k<16>};
-    hipError_t out = hipSuccess;
-    for (const void* f : fns) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        if (out == hipSuccess) out = e;
-    }
-    if (out == hipSuccess) granted = bytes;
-    return out;
+    const hipError_t e = hipFuncSetAttribute((const void*)rsf_hetdec_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) granted = bytes;
+    return e;
 }
 
 }  // namespace rsf

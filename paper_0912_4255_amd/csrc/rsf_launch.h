@@ -44,7 +44,7 @@ hipError_t launch_semico(const SemicoArgs& a, hipStream_t s);
 // spindowns [n][order] moved by D seconds along their Taylor series
 hipError_t launch_spin_translate(const double* in, double* out, int64_t n, int order, double D, hipStream_t s);
 size_t hetdec_lds(int L, int D);
-hipError_t launch_hetdec(const HetdecArgs& a, int n_cu, hipStream_t s);  // n_cu: persistent grid of the D = 64 form
+hipError_t launch_hetdec(const HetdecArgs& a, int n_cu, hipStream_t s);  // n_cu: persistent grid of the matrix-core form
 hipError_t hetdec_set_lds_limit(size_t bytes);
 
 hipError_t launch_sft_norm(const SftNormArgs& a, int n_sft, hipStream_t s);
