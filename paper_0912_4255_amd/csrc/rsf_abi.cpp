@@ -406,20 +406,30 @@ ResLayout resample_layout(const rsf_plan* p, int64_t n_sky) {
     return L;
 }
 
+// Workspace of the point entries: the flags word and FP64 partial sums
+// [candidates of a launch][n_blocks][kPointSums].  `least` is what a call must
+// have (partial sums in the coarsest split for all candidates); a call with
+// more takes its series' own split, all candidates at once or in launches of as
+// many as fit.
 struct PointLayout {
-    size_t flags, partials, total;
-    int n_blocks;
+    size_t flags, partials, per_cand, least, total;
+    int rows, n_blocks;
 };
+
+constexpr int kPointRowsMax = 32;                        // coarsest split
+constexpr size_t kPointLaunchBytes = (size_t)8 << 20;    // partial sums asked for before candidates share launches
 
 PointLayout point_layout(const rsf_plan* p, int64_t n_cand) {
     PointLayout L{};
-    size_t off = 0;
-    L.flags = off;
-    off = align_up(off + 64);
-    L.n_blocks = point_blocks((p->n + 63) / 64);
-    L.partials = off;
-    off = align_up(off + (size_t)n_cand * L.n_blocks * kPointSums * sizeof(double));
-    L.total = off;
+    const int64_t P = (p->n + 63) / 64;
+    L.flags = 0;
+    L.partials = align_up(64);
+    L.rows = point_rows(P);
+    L.n_blocks = point_blocks(P, L.rows);
+    const size_t coarse = (size_t)point_blocks(P, kPointRowsMax) * kPointSums * sizeof(double);
+    L.per_cand = (size_t)L.n_blocks * kPointSums * sizeof(double);
+    L.least = align_up(L.partials + (size_t)n_cand * coarse);
+    L.total = std::max(L.least, align_up(L.partials + std::min((size_t)n_cand * L.per_cand, kPointLaunchBytes)));
     return L;
 }
 
@@ -437,7 +447,6 @@ ResampleArgs base_resample_args(const rsf_plan* p, const rsf_segment* seg, int X
     a.x = (const float2*)seg->x[X];
     a.gaps = seg->gaps[X];
     a.n_gaps = seg->n_gaps[X];
-    // the same criterion as the point kernel's interpolated chain
     a.fast_chain = (!p->binary && 63.0 * p->d.dt * 2.0 * M_PI * std::fabs(p->eph.inv_p_sid) <= 4e-3) ? 1 : 0;
     return a;
 }
@@ -1174,8 +1183,16 @@ int point_common(const rsf_plan* p, const rsf_segment* seg, const double* theta,
         if (!(w_max * span <= 0.3))
             return fail(RSF_EINVAL, "point search needs (63 dt + max|t_m| + 100 s if binary) w_sid <= 0.3 (dt up to about 55 s)");
     }
-    const PointLayout L = point_layout(p, n);
-    if (ws_bytes < L.total) return fail(RSF_EWORKSPACE, "workspace %zu < %zu bytes", ws_bytes, L.total);
+    PointLayout L = point_layout(p, n);
+    if (ws_bytes < L.least) return fail(RSF_EWORKSPACE, "workspace %zu < %zu bytes", ws_bytes, L.total);
+    // candidates per launch in the series' split, or all in the coarsest one
+    // when not even one fits
+    int64_t step = std::min<int64_t>(n, (int64_t)((ws_bytes - L.partials) / L.per_cand));
+    if (step < 1) {
+        step = n;
+        L.rows = kPointRowsMax;
+        L.n_blocks = point_blocks((p->n + 63) / 64, L.rows);
+    }
     hipStream_t s = (hipStream_t)stream;
     char* w = (char*)ws;
     unsigned int* flags = (unsigned int*)(w + L.flags);
@@ -1183,6 +1200,7 @@ int point_common(const rsf_plan* p, const rsf_segment* seg, const double* theta,
     PointArgs a{};
     a.n = p->n;
     a.dt = p->d.dt;
+    a.inv_dt = 1.0 / p->d.dt;
     a.t_start = p->d.t_start;
     a.f_het = p->d.f_het;
     a.eph = p->eph;
@@ -1194,33 +1212,34 @@ int point_common(const rsf_plan* p, const rsf_segment* seg, const double* theta,
         a.n_gaps[X] = seg->n_gaps[X];
     }
     a.ip = p->ip;
-    a.theta = theta;
     a.order = p->spin_order;
     a.binary = p->binary ? 1 : 0;
-    // runs of 64 samples short against a sidereal day: the chain is
-    // interpolated along each run (remainder below 2e-11 s in t_m)
-    a.fast = (!p->binary && p->d.n_det == 1 && 63.0 * p->d.dt * 2.0 * M_PI * std::fabs(p->eph.inv_p_sid) <= 4e-3) ? 1 : 0;
-    a.n_cand = (int)n;
+    a.run = point_interpolates(p->d.dt, p->eph) ? 1 : 0;
+    a.rows = L.rows;
     a.P = (p->n + 63) / 64;
     a.n_blocks = L.n_blocks;
     a.partials = (double*)(w + L.partials);
     a.flags = flags;
-    // the static-scratch entry records no instrumentation events
-    const rsf_plan* tp = instrument ? p : nullptr;
-    auto run = [&](int kind, auto fn) { return tp ? timed(tp, kind, s, fn) : fn(); };
-    RSF_HIP(run(K_POINT, [&] { return launch_point(a, grad, s); }), "point launch");
     PointReduceArgs r{};
     r.partials = a.partials;
     r.n_blocks = L.n_blocks;
-    r.n_cand = (int)n;
     r.order = p->spin_order;
     r.binary = p->binary ? 1 : 0;
     r.grad = grad ? 1 : 0;
-    r.g_twoF = g_twoF;
-    r.twoF = twoF;
-    r.g_theta = g_theta;
     r.flags = flags;
-    RSF_HIP(run(K_POINT_REDUCE, [&] { return launch_point_reduce(r, s); }), "point reduce launch");
+    // the static-scratch entry records no instrumentation events
+    const rsf_plan* tp = instrument ? p : nullptr;
+    auto run = [&](int kind, auto fn) { return tp ? timed(tp, kind, s, fn) : fn(); };
+    const int width = 3 + p->spin_order + (p->binary ? 3 : 0);
+    for (int64_t c = 0; c < n; c += step) {
+        a.theta = theta + c * width;
+        a.n_cand = r.n_cand = (int)std::min<int64_t>(step, n - c);
+        r.g_twoF = g_twoF ? g_twoF + c : nullptr;
+        r.twoF = twoF ? twoF + c : nullptr;
+        r.g_theta = g_theta ? g_theta + c * width : nullptr;
+        RSF_HIP(run(K_POINT, [&] { return launch_point(a, grad, s); }), "point launch");
+        RSF_HIP(run(K_POINT_REDUCE, [&] { return launch_point_reduce(r, s); }), "point reduce launch");
+    }
     return RSF_OK;
 }
 }  // namespace
@@ -1242,14 +1261,14 @@ int rsf_fstat_backward_static(const rsf_plan* p, const rsf_segment* seg, const d
     if (n < 1 || n > 65535) return fail(RSF_EINVAL, "number of candidates must be in 1..65535");
     const hipError_t e = scratch_setup(p->device);
     if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
-    const size_t need = point_layout(p, n).total;
+    const size_t need = point_layout(p, n).least;
     if (need > kStaticScratchBytes) {
-        const size_t per = point_layout(p, 2).total - point_layout(p, 1).total;
+        const size_t per = point_layout(p, 2).least - point_layout(p, 1).least;
         return fail(RSF_EWORKSPACE,
                     "%lld candidates need %zu bytes of device scratch, above the static %zu bytes (at most %lld "
                     "candidates at this plan's length)",
                     (long long)n, need, kStaticScratchBytes,
-                    (long long)((kStaticScratchBytes - point_layout(p, 1).total) / per + 1));
+                    (long long)((kStaticScratchBytes - point_layout(p, 1).least) / per + 1));
     }
     return point_common(p, seg, theta, n, g_twoF, twoF, g_theta, g_scratch_ptr[p->device], kStaticScratchBytes,
                         stream, true, false);

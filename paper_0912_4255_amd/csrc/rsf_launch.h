@@ -62,7 +62,9 @@ hipError_t launch_sft_rows(const SftRowsArgs& a, int64_t blocks, size_t lds, int
 hipError_t launch_sft_cols(const SftColsArgs& b, int64_t blocks, size_t lds, int C, hipStream_t s);  // C in {8, 16, 32}
 hipError_t sft_set_lds_limits(size_t bytes);
 
-int point_blocks(int64_t P);
+int point_rows(int64_t P);              // 64-sample rows per wave for a series of P rows
+int point_blocks(int64_t P, int rows);  // workgroups of 4 waves per candidate
+bool point_interpolates(double dt, const EphDev& e);  // the interpolated timing chain holds at this sampling interval
 hipError_t launch_point(const PointArgs& a, bool grad, hipStream_t s);
 hipError_t launch_point_reduce(const PointReduceArgs& r, hipStream_t s);
 

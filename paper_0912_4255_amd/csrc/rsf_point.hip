@@ -26,7 +26,9 @@
 //            d_p = t_m(t_p) - R(tau_e,p) with tau_e,p + R(tau_e,p) = tau_p +
 //            t_m(t_p) changes by -(dR/dtheta_o)/(1 + R') for the orbit and by
 //            (dt_m/dtheta)/(1 + R') for the sky, R' = dR/dtau at tau_e,p.
-// Each block accumulates FP64 partial sums over 8 tiles of 1024 samples;
+// Two kernels: rsf_point_run_k interpolates the timing chain along runs of 256
+// samples and carries every ordinary call; rsf_point_k evaluates it per sample.
+// Each block accumulates FP64 partial sums over up to 128 rows of 64 samples;
 // rsf_point_reduce_k sums the blocks of a candidate in a fixed order and
 // forms 2F (eq. eq6) and the vector-Jacobian product g * d2F/dtheta.
 #include <climits>
@@ -38,7 +40,6 @@ namespace rsf {
 
 namespace {
 constexpr int kTileB = 64;
-constexpr int kTileA = 16;
 constexpr int kThreads = 256;
 constexpr int kWinMax = kTileB + kMaxTaps + 8;
 constexpr float kPiF = 3.14159265358979323846f;
@@ -371,29 +372,121 @@ __device__ __forceinline__ ChainOut chain_at(const PointArgs& A, const DetDev& D
     return c;
 }
 
-// Per-run interpolation of the chain (used when the run is short against a
-// sidereal day): the quantities that vary along a run of 64 samples (t_m,
-// a, b and, for the gradient, dT/dalpha, dT/ddelta and the sky derivatives of
-// a and b) are evaluated exactly at lanes 0, 32 and 63 and every lane takes
-// the quadratic through them, q(l) = q_0 + l d_1 + l (l - 32) d_2.  Each
-// quantity is a sum of circular motions with rate w <= 2 w_sid (the orbital
-// rate is 366 times smaller), so the remainder is at most 0.008 times the
-// third derivative's bound times (63 dt)^3, i.e. 0.008 A (2 w_sid 63 dt)^3
-// with A the amplitude: for 63 dt w_sid <= 4e-3 that is below 2e-11 s for
-// t_m (A = R_E / c) and below 5e-9 for a, b and their derivatives.
-constexpr int kChainQ = 9;                         // interpolated quantities
-constexpr int kChainRef = 13;                      // T1 and the three expansions of lane 0
-constexpr int kRunVals = 3 * kChainQ + kChainRef;  // per run: q_0, d_1, d_2, then the reference
-constexpr int kWaveRuns = kPointTiles * (kTileA / 4);
-
 }  // namespace
+
+// The sums of V values over the wave, value i in lane (i and the lanes that
+// share its upper bits) of the result: each step hands half of the values to the
+// lane across and keeps the other half, so V values take about V exchanges in
+// place of 6 V.  Returns value `lane >> (6 - LOG2)` (V <= 2^LOG2), a fixed
+// order of additions.
+template <int LOG2, int V>
+__device__ __forceinline__ double wave_sums(const double (&acc)[V], int lane) {
+    constexpr int N = 1 << LOG2;
+    static_assert(V <= N, "more values than slots");
+    double v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = i < V ? acc[i < V ? i : 0] : 0.0;
+#pragma unroll
+    for (int st = 0; st < LOG2; ++st) {
+        const int half = N >> (st + 1), off = 32 >> st;
+        const bool up = lane & off;
+#pragma unroll
+        for (int i = 0; i < half; ++i) {
+            const double keep = up ? v[i + half] : v[i], give = up ? v[i] : v[i + half];
+            v[i] = keep + __shfl_xor(give, off);
+        }
+    }
+#pragma unroll
+    for (int off = 32 >> LOG2; off > 0; off >>= 1) v[0] += __shfl_xor(v[0], off);
+    return v[0];
+}
+
+// Interpolated timing chain.  Runs of 256 consecutive resampled samples
+// (four rows of 64) take every slowly varying quantity (the delay d, the beam
+// patterns and, for the gradient, dT/dtheta and the patterns' derivatives)
+// from the quartic through five exact nodes, at s = -138.5, -85.5, 0, 85.5 and
+// 138.5 samples from the run's centre (near the Chebyshev points of the run and
+// the window around it, |s| <= kRunHalf).  Each quantity is a sum of circular
+// motions, so with rate w and H = kRunHalf dt the remainder is at most
+// A (w H)^5 / 1920, A the amplitude; the host admits sampling intervals for
+// which that is at most 1e-11 s for t_m and 4e-9 for a and b (2 w_sid), i.e.
+// dt up to 4.4 s, and orbit_interpolates() the orbits for which it is at
+// most 1e-11 s for R and 3e-11 relative for its derivatives.
+constexpr int kRunRows = 4;                      // rows of 64 samples per run
+constexpr int kRunLen = kRunRows * kTileB;
+constexpr double kRunMid = 0.5 * (kRunLen - 1);  // the centre's index in the run
+constexpr double kRunHalf = 146.0;               // samples from the centre that are interpolated
+constexpr double kNodeP = 138.5, kNodeQ = 85.5;
+constexpr int kRunsMax = 8 * 4;                  // runs of a workgroup
+// window of a run's rows: 64 samples and their compression (104 - W slots a
+// row, as the general kernel stages), and the taps
+constexpr int kRunWin = 416;
+
+__device__ __forceinline__ bool orbit_interpolates(const BinaryOrbit& b, double dt) {
+    const double x = 2.0 * kPi / b.p_orb * kRunHalf * dt;
+    return x <= 0.035 && b.a_p * (x * x) * (x * x) * x <= 1e-11 * 1920.0;
+}
+
+// Per run: quartics in s of the NQ quantities V = d / dt, a, b (and, for the
+// gradient, dT, da, db of the NS parameters that move T); the window's delay in
+// cycles, f_het d, as a quartic in x = (detector sample) - u_c; and what the
+// derivatives need beside them (below).
+template <bool GRAD, int NS>
+struct RunVals {
+    static constexpr int NQ = GRAD ? 3 + 3 * NS : 3;
+    double poly[NQ][5];
+    double het[5], u_c;
+    double G[3];                     // 1 / (1 - V'(s)) to second order
+    double psi[GRAD ? NS : 1][3];    // see rsf_point_run_k
+    double vn[5];                    // V at the nodes
+    int gap, pad;                    // 0: no sample of the run near a gap, 1: all inside one, 2: look
+};
+
+__device__ __forceinline__ double quartic(const double* c, double s) {
+    return c[0] + s * (c[1] + s * (c[2] + s * (c[3] + s * c[4])));
+}
+
+// node values at -p, -q, 0, q, p to the quartic's coefficients
+__device__ __forceinline__ void to_quartic(double* c) {
+    constexpr double p = kNodeP, q = kNodeQ, ip2 = 1.0 / (p * p), iq2 = 1.0 / (q * q), idiff = 1.0 / (p * p - q * q);
+    const double f0 = c[2];
+    const double ep = (0.5 * (c[4] + c[0]) - f0) * ip2, eq = (0.5 * (c[3] + c[1]) - f0) * iq2;
+    const double op = 0.5 * (c[4] - c[0]) * (1.0 / p), oq = 0.5 * (c[3] - c[1]) * (1.0 / q);
+    const double c4 = (ep - eq) * idiff, c3 = (op - oq) * idiff;
+    c[0] = f0;
+    c[1] = op - c3 * (p * p);
+    c[2] = ep - c4 * (p * p);
+    c[3] = c3;
+    c[4] = c4;
+}
+
+// the quartic through (x[i], y[i]) about x = 0, by divided differences; the
+// x[i] are near -p, -q, 0, q, p
+__device__ __forceinline__ void through(const double* x, const double* y, double* out) {
+    double c[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) c[i] = y[i];
+#pragma unroll
+    for (int k = 1; k < 5; ++k)
+#pragma unroll
+        for (int i = 4; i >= k; --i) c[i] = (c[i] - c[i - 1]) / (x[i] - x[i - k]);
+    double m[5] = {c[4], 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 3; k >= 0; --k) {
+#pragma unroll
+        for (int i = 4 - k; i > 0; --i) m[i] = m[i - 1] - x[k] * m[i];
+        m[0] = c[k] - x[k] * m[0];
+    }
+#pragma unroll
+    for (int i = 0; i < 5; ++i) out[i] = m[i];
+}
 
 // The binary gradient's 50 to 58 FP64 partial sums do not fit beside the rest
 // at two waves per SIMD; at one wave per SIMD its spills go to the
 // accumulation registers instead of scratch memory.
-// FAST: one detector, no orbit, runs short against a sidereal day: the
-// chain of each run is interpolated from three exact nodes.
-template <bool GRAD, int ORDER, bool BIN, bool FAST>
+// Takes the candidates that rsf_point_run_k leaves: sampling intervals too long
+// for its interpolated chain, or an orbit too fast for it.
+template <bool GRAD, int ORDER, bool BIN>
 __global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 1 : 2) void rsf_point_k(PointArgs A) {
     using SL = Slots<ORDER, BIN>;
     constexpr int NP = SL::NP;
@@ -404,8 +497,6 @@ __global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 1 : 2) void rsf_point_k(P
     __shared__ float4 win[4][kWinMax];  // z (re, im), 2 pi f_het dd_p/dalpha, 2 pi f_het dd_p/ddelta
     __shared__ float4 wino[4][(BIN && GRAD) ? kWinMax : 1];  // 2 pi f_het dd_p/d(a_p, P_b, t_asc)
     __shared__ double red[4][kPointSums];
-    __shared__ double runs[4][FAST ? kWaveRuns : 1][FAST ? kRunVals : 1];
-    static_assert(!(FAST && BIN), "the interpolated chain is for isolated sources");
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -422,6 +513,7 @@ __global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 1 : 2) void rsf_point_k(P
         const BinaryOrbit given{th[3 + ORDER], th[4 + ORDER], th[5 + ORDER]};
         orbit_ok = orbit_admitted(given);
         bo = orbit_or_none(given);
+        if (A.run && orbit_ok && orbit_interpolates(bo, A.dt)) return;
     }
     double sa, ca, sd, cd;
     sincos(al, &sa, &ca);
@@ -455,7 +547,7 @@ __global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 1 : 2) void rsf_point_k(P
     RunAngles ra;
     double s_dl, c_dl, s_dg, c_dg;
     {
-        const int64_t k_first = ((int64_t)blockIdx.x * kPointTiles * kTileA + wave) * kTileB;
+        const int64_t k_first = ((int64_t)blockIdx.x * A.rows * 4 + wave) * kTileB;
         const double tau0 = A.t_start + (double)k_first * A.dt;
         sincos(A.eph.lambda0 + 2.0 * kPi * frac_rev(tau0 * A.eph.inv_p_orb), &ra.sl, &ra.cl);
         sincos(A.eph.theta0 + 2.0 * kPi * frac_rev(tau0 * A.eph.inv_p_sid), &ra.sg, &ra.cg);
@@ -464,66 +556,9 @@ __global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 1 : 2) void rsf_point_k(P
         sincos(w_sid * dtau, &s_dg, &c_dg);
     }
 
-    if constexpr (FAST) {
-        // nodes: lanes 0, 32, 63 of each of this wave's runs (run rr is row
-        // wave + 4 (rr % 4) of tile rr / 4), the chain evaluated exactly
-        const DetDev& D = A.det[0];
-        for (int nd = lane; nd < 3 * kWaveRuns; nd += 64) {
-            const int rr = nd / 3, m = nd - 3 * (nd / 3);
-            const int off = m == 0 ? 0 : (m == 1 ? 32 : 63);
-            const int64_t row = ((int64_t)blockIdx.x * kPointTiles + rr / 4) * kTileA + wave + 4 * (rr % 4);
-            const double tau_run = A.t_start + (double)(row * kTileB) * A.dt;
-            RunAngles rn;
-            sincos(A.eph.lambda0 + 2.0 * kPi * frac_rev(tau_run * A.eph.inv_p_orb), &rn.sl, &rn.cl);
-            sincos(A.eph.theta0 + 2.0 * kPi * frac_rev(tau_run * A.eph.inv_p_sid), &rn.sg, &rn.cg);
-            const double tb = (double)(row * kTileB + off) * A.dt;
-            const ChainOut c = chain_at<GRAD, false>(A, D, rn, (double)off * A.dt, tb, geo, bo, wo, w_sid);
-            double* v = runs[wave][rr] + m * kChainQ;
-            v[0] = tb - c.T;
-            v[1] = c.av;
-            v[2] = c.bv;
-            v[3] = c.dTa;
-            v[4] = c.dTd;
-            v[5] = c.daa;
-            v[6] = c.dad;
-            v[7] = c.dba;
-            v[8] = c.dbd;
-            if (m == 0) {
-                double* rf = runs[wave][rr] + 3 * kChainQ;
-                rf[0] = c.T1;
-                rf[1] = c.x0.tm;
-                rf[2] = c.x0.d1;
-                rf[3] = c.x0.d2;
-                rf[4] = c.x0.d3;
-                rf[5] = c.xa.tm;
-                rf[6] = c.xa.d1;
-                rf[7] = c.xa.d2;
-                rf[8] = c.xa.d3;
-                rf[9] = c.xd.tm;
-                rf[10] = c.xd.d1;
-                rf[11] = c.xd.d2;
-                rf[12] = c.xd.d3;
-            }
-        }
-        __syncthreads();
-        // node values (q_0, q_32, q_63) to Newton coefficients (q_0, d_1, d_2)
-        if (lane < kWaveRuns) {
-            double* v = runs[wave][lane];
-#pragma unroll
-            for (int i = 0; i < kChainQ; ++i) {
-                const double q0 = v[i], q32 = v[kChainQ + i], q63 = v[2 * kChainQ + i];
-                const double d1 = (q32 - q0) * (1.0 / 32.0);
-                v[kChainQ + i] = d1;
-                v[2 * kChainQ + i] = ((q63 - q32) * (1.0 / 31.0) - d1) * (1.0 / 63.0);
-            }
-        }
-        __syncthreads();
-    }
-
-    for (int tile = 0; tile < kPointTiles; ++tile) {
-        const int64_t a0 = ((int64_t)blockIdx.x * kPointTiles + tile) * kTileA;
-        for (int r = 0; r < kTileA / 4; ++r) {
-            const int64_t row = a0 + wave + 4 * r;
+    {
+        for (int r = 0; r < A.rows; ++r) {
+            const int64_t row = ((int64_t)blockIdx.x * A.rows + r) * 4 + wave;
             const int64_t k = row * kTileB + lane;
             const bool valid = (row < A.P) && (k < A.n);
             const double tb = (double)k * A.dt;
@@ -536,46 +571,20 @@ __global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 1 : 2) void rsf_point_k(P
                 ChainOut c{};
                 double t_ref;
                 RoemerD q0, qa{}, qd{};
-                if constexpr (FAST) {
-                    // the run's quadratic through its nodes at lanes 0, 32, 63
-                    const double* nd = runs[wave][tile * (kTileA / 4) + r];
-                    const double l = (double)lane, b = l * (l - 32.0);
-                    auto at = [&](int i) { return nd[i] + l * nd[kChainQ + i] + b * nd[2 * kChainQ + i]; };
-                    tm = at(0);
-                    c.av = at(1);
-                    c.bv = at(2);
-                    if (GRAD) {
-                        c.dTa = at(3);
-                        c.dTd = at(4);
-                        c.daa = at(5);
-                        c.dad = at(6);
-                        c.dba = at(7);
-                        c.dbd = at(8);
-                    }
-                    const double* rf = nd + 3 * kChainQ;
-                    t_ref = rf[0];
-                    q0 = RoemerD{rf[1], rf[2], rf[3], rf[4]};
-                    if (GRAD) {
-                        qa = RoemerD{rf[5], rf[6], rf[7], rf[8]};
-                        qd = RoemerD{rf[9], rf[10], rf[11], rf[12]};
-                    }
-                    T = tb - tm;
-                } else {
-                    if (valid) {
-                        c = chain_at<GRAD, BIN>(A, D, ra, (double)lane * A.dt, tb, geo, bo, wo, w_sid);
-                        T = c.T;
-                        tm = tb - T;
-                    }
-                    // expansion point of t_m (and of its sky derivatives) for the
-                    // window: the first valid lane's fixed-point iterate
-                    const uint64_t vmask = __ballot(valid);
-                    const int src = vmask ? __ffsll((long long)vmask) - 1 : 0;
-                    t_ref = readlane_d(c.T1, src);
-                    q0 = readlane_rd(c.x0, src);
-                    if (GRAD) {
-                        qa = readlane_rd(c.xa, src);
-                        qd = readlane_rd(c.xd, src);
-                    }
+                if (valid) {
+                    c = chain_at<GRAD, BIN>(A, D, ra, (double)lane * A.dt, tb, geo, bo, wo, w_sid);
+                    T = c.T;
+                    tm = tb - T;
+                }
+                // expansion point of t_m (and of its sky derivatives) for the
+                // window: the first valid lane's fixed-point iterate
+                const uint64_t vmask = __ballot(valid);
+                const int src = vmask ? __ffsll((long long)vmask) - 1 : 0;
+                t_ref = readlane_d(c.T1, src);
+                q0 = readlane_rd(c.x0, src);
+                if (GRAD) {
+                    qa = readlane_rd(c.xa, src);
+                    qd = readlane_rd(c.xd, src);
                 }
                 if (valid) {
                     const double u = T / A.dt;
@@ -840,32 +849,475 @@ __global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 1 : 2) void rsf_point_k(P
     }
 }
 
+// 2F's partial sums (and the gradient's) with the interpolated timing chain.
+// Per run of 256 samples and detector:
+//   * the nodes of all the workgroup's runs are evaluated first, one per thread
+//     (chain_at), and turned into quartics;
+//   * the run's detector samples are heterodyne-corrected once into the wave's
+//     window in LDS, the delay at a detector sample from its own quartic;
+//   * every sample interpolates z~ with w, and for the gradient also the sums
+//     with w' (s1) and with the kernel's first moment (m1 = sum w_p (p - u) z_p;
+//     for an orbit the second, m2, too).  The heterodyne correction's derivative
+//     is smooth over the window, so its sum is its value at u times z~ plus
+//     its slope times m1 (plus half its curvature times m2):
+//       dz~/dtheta = s1 dT/dt - i (2 pi f_het D z~ + psi m1 + chi m2 / 2),
+//     D = (dd/dtheta at fixed T) = -dT (1 + dd/dT) = -dT G, since d(T; theta) =
+//     t_b - T along the inversion; psi = 2 pi f_het dD/du, chi = 2 pi f_het
+//     d2D/du2 in samples.  For an isolated source D's curvature (1e-10 s per
+//     sample^2 on 500 s) is far below FP32.
+//     For the Dirichlet kernel of a long series w = (-1)^m sin(pi f) / (pi x),
+//     so z~, s1 and m1 are sums of (-1)^m z / x, (-1)^m z / x^2 and (-1)^m z; the
+//     two taps next to u keep the series form near x = 0.
+// What bounds it: vector issue.  128 candidates of 1,728,000 samples: 3.40 ms with
+// the gradient and 1.78 ms without, against 9.33 and 5.35 ms for quadratics per
+// 64 samples with the correction's derivatives per window sample and tap; 16
+// binary candidates: 0.88 and 0.27 ms against 4.17 and 1.72 ms (every sample's
+// chain and two Newton steps per window sample); one candidate of 21,600 samples
+// at 4 s: 14.5 and 12.7 us against 202 and 145 us (three workgroups).
+template <bool GRAD, int ORDER, bool BIN>
+__global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 2 : (GRAD ? 3 : 4)) void rsf_point_run_k(PointArgs A) {
+    using SL = Slots<ORDER, BIN>;
+    constexpr int NP = SL::NP, NS = SL::NS;
+    constexpr int S_FA = SL::FA, S_FB = SL::FB, S_A = SL::A, S_B = SL::B, S_C = SL::C;
+    constexpr int S_DFA = SL::DFA, S_DFB = SL::DFB, S_DA = SL::DA, S_DB = SL::DB, S_DC = SL::DC;
+    constexpr int S_SKY = 2 * (1 + ORDER);  // offset of the parameters that move T within S_DFA / S_DFB
+    constexpr int NSUM = GRAD ? SL::USED : S_DFA;
+    constexpr int LOG2 = NSUM <= 8 ? 3 : NSUM <= 32 ? 5 : 6;
+    using RV = RunVals<GRAD, NS>;
+    constexpr int NQ = RV::NQ;
+    __shared__ RV runs[kRunsMax];
+    __shared__ float2 win[4][kRunWin];
+    __shared__ double red[4][kPointSums];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cand = blockIdx.y;
+    const double* th = A.theta + (int64_t)NP * cand;
+    BinaryOrbit bo{};
+    if constexpr (BIN) {
+        bo = BinaryOrbit{th[3 + ORDER], th[4 + ORDER], th[5 + ORDER]};
+        if (!orbit_admitted(bo) || !orbit_interpolates(bo, A.dt)) return;  // rsf_point_k's
+    }
+    const double f = th[0];
+    double fs[ORDER];  // f^(1) .. f^(ORDER)
+#pragma unroll
+    for (int i = 0; i < ORDER; ++i) fs[i] = th[1 + i];
+    const int W = A.ip.taps, hw = W / 2;
+    const float pin = kPiF / (float)A.ip.n;
+    const bool dir_series = A.ip.kernel == 1 && pin * (float)(hw + 1) < 0.01f;
+    // pi x / n < 2.9e-4 on every tap: g = 1 and g' pi / n = 0 to FP32 precision
+    const bool dir_flat = A.ip.kernel == 1 && pin * (float)(hw + 1) < 2.9e-4f;
+    // rows of this workgroup: with one row per wave the four waves share a run
+    const int n_runs = max(1, A.rows / kRunRows) * (A.rows >= kRunRows ? 4 : 1);
+    const int64_t row_b = (int64_t)blockIdx.x * 4 * A.rows;  // first row
+
+    double acc[NSUM];
+#pragma unroll
+    for (int i = 0; i < NSUM; ++i) acc[i] = 0.0;
+    bool overflow = false;
+
+    for (int X = 0; X < A.n_det; ++X) {
+        const DetDev& D = A.det[X];
+        // nodes
+        __syncthreads();
+        if (tid < 5 * n_runs) {
+            const int rr = tid / 5, i = tid - 5 * rr;
+            double sa, ca, sd, cd;
+            sincos(th[1 + ORDER], &sa, &ca);
+            sincos(th[2 + ORDER], &sd, &cd);
+            SkyGeom geo;
+            geo.n0 = make_double3(cd * ca, cd * sa, sd);
+            geo.n0a = make_double3(-cd * sa, cd * ca, 0.0);
+            geo.n0d = make_double3(-sd * ca, -sd * sa, cd);
+            geo.pp = make_double3(-sa, ca, 0.0);
+            geo.qq = geo.n0d;
+            geo.pa = make_double3(-ca, -sa, 0.0);
+            geo.qa = make_double3(sd * sa, -sd * ca, 0.0);
+            geo.qd = make_double3(-cd * ca, -cd * sa, -sd);
+            const double s = i == 0 ? -kNodeP : i == 1 ? -kNodeQ : i == 2 ? 0.0 : i == 3 ? kNodeQ : kNodeP;
+            const double tb = ((double)((row_b + (int64_t)rr * kRunRows) * kTileB) + (kRunMid + s)) * A.dt;
+            const double tau = A.t_start + tb;
+            RunAngles ra;
+            sincos(A.eph.lambda0 + 2.0 * kPi * frac_rev(tau * A.eph.inv_p_orb), &ra.sl, &ra.cl);
+            sincos(A.eph.theta0 + 2.0 * kPi * frac_rev(tau * A.eph.inv_p_sid), &ra.sg, &ra.cg);
+            const ChainOut c = chain_at<GRAD, BIN>(A, D, ra, 0.0, tb, geo, bo, 2.0 * kPi * A.eph.inv_p_orb,
+                                                   2.0 * kPi * A.eph.inv_p_sid);
+            RV& v = runs[rr];
+            const double V = (tb - c.T) / A.dt;
+            v.vn[i] = V;
+            v.poly[0][i] = V;
+            v.poly[1][i] = c.av;
+            v.poly[2][i] = c.bv;
+            if constexpr (GRAD) {
+                v.poly[3][i] = c.dTa;
+                v.poly[4][i] = c.dTd;
+                v.poly[3 + NS][i] = c.daa;
+                v.poly[4 + NS][i] = c.dad;
+                v.poly[3 + 2 * NS][i] = c.dba;
+                v.poly[4 + 2 * NS][i] = c.dbd;
+                if constexpr (BIN) {
+#pragma unroll
+                    for (int o = 0; o < 3; ++o) {
+                        v.poly[5 + o][i] = c.dTo[o];
+                        v.poly[5 + NS + o][i] = c.dao[o];
+                        v.poly[5 + 2 * NS + o][i] = c.dbo[o];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        // quartics, one quantity per thread; the window's delay is the last
+        for (int e = tid; e < n_runs * (NQ + 1); e += kThreads) {
+            const int rr = e / (NQ + 1), qi = e - rr * (NQ + 1);
+            RV& v = runs[rr];
+            if (qi < NQ) {
+                to_quartic(v.poly[qi]);
+            } else {
+                double x[5], y[5];
+                const double uc = (double)((row_b + (int64_t)rr * kRunRows) * kTileB) + kRunMid - v.vn[2];
+                const double at[5] = {-kNodeP, -kNodeQ, 0.0, kNodeQ, kNodeP};
+#pragma unroll
+                for (int i = 0; i < 5; ++i) {
+                    x[i] = at[i] - (v.vn[i] - v.vn[2]);
+                    y[i] = A.f_het * (v.vn[i] * A.dt);
+                }
+                through(x, y, v.het);
+                v.u_c = uc;
+            }
+        }
+        __syncthreads();
+        if (tid < n_runs) {
+            RV& v = runs[tid];
+            const double* V = v.poly[0];
+            // G = 1 / (1 - V'): V' = V1 + 2 V2 s + 3 V3 s^2
+            const double G = 1.0 / (1.0 - V[1]), G2 = G * G;
+            v.G[0] = G;
+            v.G[1] = 2.0 * V[2] * G2;
+            v.G[2] = (3.0 * V[3] + 4.0 * V[2] * V[2] * G) * G2;
+            if constexpr (GRAD) {
+                const double k = -2.0 * kPi * A.f_het * G2;
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {
+                    const double* t = v.poly[3 + i];
+                    // psi = 2 pi f_het dD/du and its slope along the run, chi / 2
+                    v.psi[i][0] = k * (t[1] + t[0] * (2.0 * V[2]) * G);
+                    v.psi[i][1] = k * (2.0 * t[2] + 3.0 * t[1] * (2.0 * V[2]) + t[0] * (6.0 * V[3]));
+                    v.psi[i][2] = k * t[2] * G;
+                }
+            }
+            // gaps: does one start or end near the run's samples (nearest-sample
+            // mask), or are all of them inside one?
+            const double k0 = (double)((row_b + (int64_t)tid * kRunRows) * kTileB);
+            const int64_t lo = (int64_t)floor(k0 - quartic(V, -kRunMid)) - 2;
+            const int64_t hi = (int64_t)floor(k0 + (kRunLen - 1) - quartic(V, kRunMid)) + 3;
+            const int64_t* gaps = A.gaps[X];
+            int b = -1;  // last gap that starts at or before hi
+            for (int l = 0, h = A.n_gaps[X] - 1; l <= h;) {
+                const int mid = (l + h) >> 1;
+                if (gaps[2 * mid] <= hi) {
+                    b = mid;
+                    l = mid + 1;
+                } else {
+                    h = mid - 1;
+                }
+            }
+            int state = 0;
+            if (b >= 0) {
+                const int64_t s0 = gaps[2 * b], e0 = gaps[2 * b + 1];
+                state = e0 <= lo ? 0 : (s0 <= lo && e0 > hi) ? 1 : 2;
+            }
+            v.gap = state;
+        }
+        __syncthreads();
+
+        for (int rr0 = 0; rr0 < n_runs; rr0 += 4) {
+            const int rr = A.rows >= kRunRows ? wave * (n_runs / 4) + rr0 / 4 : 0;
+            const int r0 = A.rows >= kRunRows ? 0 : wave, r1 = A.rows >= kRunRows ? kRunRows : wave + 1;
+            const RV& v = runs[rr];
+            const int64_t k_run = (row_b + (int64_t)rr * kRunRows) * kTileB;  // the run's first sample
+            const int last = (int)min((int64_t)(r1 * kTileB), A.n - k_run) - 1;  // last valid index in the run
+            if (last < r0 * kTileB) continue;
+            // detector-grid window of these rows, heterodyne-corrected
+            const double V0 = quartic(v.poly[0], (double)(r0 * kTileB) - kRunMid);
+            const double V1 = quartic(v.poly[0], (double)last - kRunMid);
+            const int64_t j0 = (int64_t)floor((double)(k_run + r0 * kTileB) - V0);
+            const int64_t j1 = (int64_t)floor((double)(k_run + last) - V1);
+            const int64_t w0 = j0 - hw + 1;
+            const int64_t wlen64 = j1 - j0 + W;
+            const bool ok = j1 >= j0 && wlen64 <= (r1 - r0) * (104 - W) + W;
+            const int wlen = ok ? (int)wlen64 : 0;
+            if (!ok) overflow = true;
+            const float2* xs = A.x[X];
+            const double xc = (double)w0 - v.u_c;
+            for (int p0 = 0; p0 < wlen; p0 += 320) {
+                float2 xv[5];
+#pragma unroll
+                for (int q = 0; q < 5; ++q) {
+                    const int p = p0 + 64 * q + lane;
+                    const int64_t jj = w0 + p;
+                    xv[q] = (p < wlen && jj >= 0 && jj < A.n) ? xs[jj] : make_float2(0.f, 0.f);
+                }
+#pragma unroll
+                for (int q = 0; q < 5; ++q) {
+                    const int p = p0 + 64 * q + lane;
+                    if (p0 + 64 * q < wlen) {
+                        const double cyc = quartic(v.het, xc + (double)p);
+                        const float ph = (float)(cyc - rint(cyc));
+                        const float sn = __builtin_amdgcn_sinf(ph), cs = __builtin_amdgcn_cosf(ph);  // revolutions
+                        if (p < wlen)
+                            win[wave][p] = make_float2(xv[q].x * cs + xv[q].y * sn, xv[q].y * cs - xv[q].x * sn);
+                    }
+                }
+            }
+            // the window is this wave's own: its LDS operations complete in
+            // order, so a wave-level barrier suffices
+            __builtin_amdgcn_wave_barrier();
+            for (int r = r0; r < r1; ++r) {
+                const int l = r * kTileB + lane;
+                if (l > last) continue;
+                const int64_t k = k_run + l;
+                const double s = (double)l - kRunMid;
+                const double V = quartic(v.poly[0], s);
+                const double u = (double)k - V, fl = floor(u);
+                const float frac = (float)(u - fl);
+                const int base = (int)((int64_t)fl - hw + 1 - w0);  // slot of tap 1
+                if (!ok || base < 0 || base + W > wlen) {
+                    overflow = true;
+                    acc[S_FA] = __longlong_as_double(0x7ff8000000000000LL);
+                    continue;
+                }
+                const float2* wz = win[wave] + base;
+                float2 zt, s1 = make_float2(0.f, 0.f), m1 = s1, m2 = s1;
+                const float sf = __builtin_amdgcn_sinf(0.5f * frac), cf = __builtin_amdgcn_cosf(0.5f * frac);
+                if (dir_flat) {
+                    // taps hw (x = frac) and hw + 1 (x = frac - 1)
+                    float w0_, dw0, w1_, dw1;
+                    const float x1 = frac - 1.f;
+                    sinc_d(frac, sf, cf, w0_, dw0);
+                    sinc_d(x1, -sf, -cf, w1_, dw1);
+                    const float2 za = wz[hw - 1], zb = wz[hw];
+                    float2 a1 = make_float2(0.f, 0.f), a2 = a1, a0 = a1, ax = a1;
+                    // taps hw - m (x = frac + m, sign (-1)^m) and hw + 1 + m (x = frac - 1 - m, sign -(-1)^m)
+                    auto pair = [&](int m, float sg) {
+                        const float2 zl = wz[hw - 1 - m], zr = wz[hw + m];
+                        const float xl = frac + (float)m, xr = x1 - (float)m;
+                        const float rl = sg * __builtin_amdgcn_rcpf(xl), rx = -sg * __builtin_amdgcn_rcpf(xr);
+                        a1.x += rl * zl.x + rx * zr.x;
+                        a1.y += rl * zl.y + rx * zr.y;
+                        if (GRAD) {
+                            // (-1)^m / x^2 = sg rl^2, and -sg rx^2 on the right
+                            const float ql = sg * rl * rl, qr = -sg * rx * rx;
+                            a2.x += ql * zl.x + qr * zr.x;
+                            a2.y += ql * zl.y + qr * zr.y;
+                            a0.x += sg * (zl.x - zr.x);
+                            a0.y += sg * (zl.y - zr.y);
+                            if constexpr (BIN) {
+                                ax.x += sg * (xl * zl.x - xr * zr.x);
+                                ax.y += sg * (xl * zl.y - xr * zr.y);
+                            }
+                        }
+                    };
+                    int m = 1;
+                    for (; m + 1 < hw; m += 2) {
+                        pair(m, -1.f);
+                        pair(m + 1, 1.f);
+                    }
+                    if (m < hw) pair(m, -1.f);
+                    const float sp = sf * (1.f / kPiF);
+                    zt = make_float2(sp * a1.x + (w0_ * za.x + w1_ * zb.x), sp * a1.y + (w0_ * za.y + w1_ * zb.y));
+                    if (GRAD) {
+                        s1 = make_float2(cf * a1.x - sp * a2.x + (dw0 * za.x + dw1 * zb.x),
+                                         cf * a1.y - sp * a2.y + (dw0 * za.y + dw1 * zb.y));
+                        // w (p - u) = -w x = -(-1)^m sin(pi f) / pi
+                        m1 = make_float2(-sp * (a0.x + za.x - zb.x), -sp * (a0.y + za.y - zb.y));
+                        if constexpr (BIN)
+                            m2 = make_float2(sp * (ax.x + frac * za.x - x1 * zb.x), sp * (ax.y + frac * za.y - x1 * zb.y));
+                    }
+                } else {
+                    zt = make_float2(0.f, 0.f);
+                    for (int i = 1; i <= W; ++i) {
+                        const float x = frac + (float)(hw - i);
+                        const bool odd = (hw - i) & 1;
+                        const float sx = odd ? -sf : sf, cx = odd ? -cf : cf;  // sin, cos of pi x
+                        float w, dw = 0.f;
+                        if (x == 0.f) {
+                            w = 1.f;
+                        } else if (dir_series) {
+                            // Dirichlet kernel of a long series: sinc(x) g(y), y = pi x / n
+                            // small, g = y / tan(y) (n even) or y / sin(y) (n odd) as a series
+                            float s0, ds0;
+                            sinc_d(x, sx, cx, s0, ds0);
+                            const float y = x * pin, y2 = y * y;
+                            const float g = A.ip.n_odd ? 1.f + y2 * (1.f / 6.f + y2 * (7.f / 360.f))
+                                                       : 1.f - y2 * (1.f / 3.f + y2 * (1.f / 45.f));
+                            w = s0 * g;
+                            if (GRAD) {
+                                const float dg = A.ip.n_odd ? y * (1.f / 3.f + y2 * (7.f / 90.f))
+                                                            : -y * (2.f / 3.f + y2 * (4.f / 45.f));
+                                dw = ds0 * g + s0 * dg * pin;
+                            }
+                        } else {
+                            kernel_w<GRAD>(A.ip, x, sx, cx, w, dw);
+                        }
+                        const float2 zz = wz[i - 1];
+                        zt.x += w * zz.x;
+                        zt.y += w * zz.y;
+                        if (GRAD) {
+                            s1.x += dw * zz.x;
+                            s1.y += dw * zz.y;
+                            const float wx = w * x;
+                            m1.x -= wx * zz.x;
+                            m1.y -= wx * zz.y;
+                            if constexpr (BIN) {
+                                m2.x += wx * x * zz.x;
+                                m2.y += wx * x * zz.y;
+                            }
+                        }
+                    }
+                }
+                bool mk = v.gap != 1;
+                {
+                    const double fn = floor(u + 0.5);
+                    mk = mk && fn >= 0.0 && fn < (double)A.n;
+                    if (v.gap == 2) mk = mk && !in_gap(A.gaps[X], A.n_gaps[X], (int64_t)fn);
+                }
+                // total phase: spindown Phi_s and the Fourier kernel at f;
+                // us[j] = T^(j+2)/(j+2)! + d T^(j+1)/(j+1)! (cycles per unit f^(j+1))
+                const double tb = (double)k * A.dt, d = V * A.dt, T = tb - d;
+                double us[ORDER];
+                double cyc = (f - A.f_het) * tb;
+                if constexpr (ORDER == 1) {
+                    us[0] = 0.5 * (tb * tb - d * d);
+                    cyc += fs[0] * us[0];
+                } else {
+                    double Tj = T;  // T^(j+1)
+#pragma unroll
+                    for (int i = 0; i < ORDER; ++i) {
+                        us[i] = Tj * T * kInvFact[i + 2] + d * Tj * kInvFact[i + 1];
+                        cyc += fs[i] * us[i];
+                        Tj *= T;
+                    }
+                }
+                const float ph = (float)(cyc - rint(cyc));
+                const float sn = __builtin_amdgcn_sinf(ph), cs = __builtin_amdgcn_cosf(ph);  // revolutions
+                // times exp(-2 pi i cyc)
+                auto turn = [&](float2 z, double& re, double& im) {
+                    re = (double)(z.x * cs + z.y * sn);
+                    im = (double)(z.y * cs - z.x * sn);
+                };
+                double zr, zi;
+                turn(zt, zr, zi);
+                const double av = quartic(v.poly[1], s), bv = quartic(v.poly[2], s);
+                const double wa = D.w * av, wb = D.w * bv;
+                acc[S_FA + 0] += wa * zr;
+                acc[S_FA + 1] += wa * zi;
+                acc[S_FB + 0] += wb * zr;
+                acc[S_FB + 1] += wb * zi;
+                if (mk) {
+                    acc[S_A] += wa * av;
+                    acc[S_B] += wb * bv;
+                    acc[S_C] += wa * bv;
+                }
+                if constexpr (GRAD) {
+                    // d/df: -2 pi i t_b, d/df^(j): -2 pi i us[j-1]; (-i c)(x + i y) = c y - i c x
+                    auto phase_slope = [&](int i, double c) {
+                        const double x = c * zi, y = -c * zr;
+                        acc[S_DFA + 2 * i] += wa * x;
+                        acc[S_DFA + 2 * i + 1] += wa * y;
+                        acc[S_DFB + 2 * i] += wb * x;
+                        acc[S_DFB + 2 * i + 1] += wb * y;
+                    };
+                    phase_slope(0, 2.0 * kPi * tb);
+                    // dPhi_s/dT / (2 pi d) = sum_j f^(j) T^(j-1)/(j-1)!
+                    double rate = 0.0, Tj = 1.0;
+#pragma unroll
+                    for (int i = 0; i < ORDER; ++i) {
+                        phase_slope(1 + i, 2.0 * kPi * us[i]);
+                        rate += fs[i] * Tj * kInvFact[i];
+                        Tj *= T;
+                    }
+                    double sr, si, mr, mi, nr = 0.0, ni = 0.0;
+                    turn(s1, sr, si);
+                    turn(m1, mr, mi);
+                    if constexpr (BIN) turn(m2, nr, ni);
+                    // everything proportional to dT: s1 / dt - i H z~, with
+                    // H = -2 pi f_het G + 2 pi rate d
+                    double G = v.G[0] + s * v.G[1];
+                    if constexpr (BIN) G += s * s * v.G[2];
+                    const double H = 2.0 * kPi * (rate * d - A.f_het * G), inv_dt = A.inv_dt;
+                    const double Qr = sr * inv_dt + H * zi, Qi = si * inv_dt - H * zr;
+#pragma unroll
+                    for (int i = 0; i < NS; ++i) {
+                        const double dT = quartic(v.poly[3 + i], s);
+                        const double da = D.w * quartic(v.poly[3 + NS + i], s);
+                        const double db = D.w * quartic(v.poly[3 + 2 * NS + i], s);
+                        double psi = v.psi[i][0];
+                        if constexpr (BIN) psi += s * v.psi[i][1];
+                        double Pr = dT * Qr + psi * mi, Pi = dT * Qi - psi * mr;
+                        if constexpr (BIN) {
+                            Pr += v.psi[i][2] * ni;
+                            Pi -= v.psi[i][2] * nr;
+                        }
+                        acc[S_DFA + S_SKY + 2 * i] += da * zr + wa * Pr;
+                        acc[S_DFA + S_SKY + 2 * i + 1] += da * zi + wa * Pi;
+                        acc[S_DFB + S_SKY + 2 * i] += db * zr + wb * Pr;
+                        acc[S_DFB + S_SKY + 2 * i + 1] += db * zi + wb * Pi;
+                        if (mk) {
+                            acc[S_DA + i] += 2.0 * da * av;
+                            acc[S_DB + i] += 2.0 * db * bv;
+                            acc[S_DC + i] += da * bv + db * av;
+                        }
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();  // the next run rewrites this wave's window
+        }
+    }
+    if (__any(overflow) && lane == 0) atomicOr(A.flags, 2u);
+
+    // workgroup sums in a fixed order
+    const double t = wave_sums<LOG2>(acc, lane);
+    const int slot = lane >> (6 - LOG2);
+    if ((lane & ((1 << (6 - LOG2)) - 1)) == 0 && slot < NSUM) red[wave][slot] = t;
+    __syncthreads();
+    if (tid < NSUM)
+        A.partials[((int64_t)cand * A.n_blocks + blockIdx.x) * kPointSums + tid] =
+            ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+}
+
 // One workgroup per candidate: fixed-order sum of the block partials, then
 // 2F = 2Q/D with Q = B|Fa|^2 + A|Fb|^2 - 2C Re(Fa Fb^*), D = AB - C^2, and
 // d2F = 2 (dQ D - Q dD) / D^2.
+// Thread (group, slot): a group's threads read whole rows of partial sums, the
+// 16 groups stride over the rows, and their sums are added in a fixed order
+// (one slot after another with a tree of 256 threads each took 15 to 26 us).
 template <int ORDER, bool BIN>
-__global__ __launch_bounds__(256) void rsf_point_reduce_k(PointReduceArgs R) {
+__global__ __launch_bounds__(1024) void rsf_point_reduce_k(PointReduceArgs R) {
     using SL = Slots<ORDER, BIN>;
     constexpr int NP = SL::NP;
     constexpr int S_FA = SL::FA, S_FB = SL::FB, S_A = SL::A, S_B = SL::B, S_C = SL::C;
     constexpr int S_DFA = SL::DFA, S_DFB = SL::DFB, S_DA = SL::DA, S_DB = SL::DB, S_DC = SL::DC;
-    __shared__ double red[256];
+    constexpr int kGroups = 1024 / kPointSums;
+    __shared__ double part[kGroups][kPointSums];
     __shared__ double tot[kPointSums];
     const int cand = blockIdx.x;
     const int nsum = R.grad ? SL::USED : S_DFA;
+    const int slot = threadIdx.x % kPointSums, group = threadIdx.x / kPointSums;
     const double* p = R.partials + (int64_t)cand * R.n_blocks * kPointSums;
-    for (int i = 0; i < nsum; ++i) {
-        double s = 0.0;
-        for (int b = threadIdx.x; b < R.n_blocks; b += 256) s += p[(int64_t)b * kPointSums + i];
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int h = 128; h > 0; h >>= 1) {
-            if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) tot[i] = red[0];
-        __syncthreads();
+    {
+        double v = 0.0;
+        if (slot < nsum)
+            for (int b = group; b < R.n_blocks; b += kGroups) v += p[(int64_t)b * kPointSums + slot];
+        part[group][slot] = v;
     }
+    __syncthreads();
+    if (threadIdx.x < kPointSums) {
+        double v = 0.0;
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) v += part[g][threadIdx.x];
+        tot[threadIdx.x] = v;
+    }
+    __syncthreads();
     if (threadIdx.x != 0) return;
     const double Far = tot[S_FA], Fai = tot[S_FA + 1], Fbr = tot[S_FB], Fbi = tot[S_FB + 1];
     const double Aa = tot[S_A], Bb = tot[S_B], Cc = tot[S_C];
@@ -896,40 +1348,56 @@ __global__ __launch_bounds__(256) void rsf_point_reduce_k(PointReduceArgs R) {
     }
 }
 
-int point_blocks(int64_t P) { return (int)((P + kTileA * kPointTiles - 1) / (kTileA * kPointTiles)); }
+// Rows of 64 samples per wave: whole runs of four rows, eight runs for long
+// series (the node chain and the sums of a workgroup are shared by 128 rows)
+// down to one, so that a candidate alone has around 128 to 256 workgroups; very
+// short series put one row on each wave (n = 21,600: 85 workgroups instead of
+// 22).  A candidate's split depends on the series alone: its result does not
+// change with the number of candidates in a call.
+int point_rows(int64_t P) { return P <= 512 ? 1 : P <= 4096 ? 4 : P <= 8192 ? 8 : P <= 16384 ? 16 : 32; }
+int point_blocks(int64_t P, int rows) { return (int)((P + 4 * rows - 1) / (4 * rows)); }
+
+bool point_interpolates(double dt, const EphDev& e) {
+    const double H = kRunHalf * dt;
+    const double xo = 2.0 * kPi * fabs(e.inv_p_orb) * H, xs = 2.0 * kPi * fabs(e.inv_p_sid) * H;
+    auto p5 = [](double x) { return x * x * x * x * x / 1920.0; };
+    return fabs(e.au_c) * p5(xo) + fabs(e.re_c) * p5(xs) <= 1e-11 && p5(2.0 * xs) <= 4e-9 && xo <= 0.1;
+}
 
 hipError_t launch_point(const PointArgs& a, bool grad, hipStream_t s) {
     const dim3 grid((unsigned)a.n_blocks, (unsigned)a.n_cand);
-#define RSF_POINT(G, O, B, F) hipLaunchKernelGGL((rsf_point_k<G, O, B, F>), grid, dim3(kThreads), 0, s, a)
-    const bool fast = a.fast && !a.binary && a.n_det == 1;
-    switch (a.order * 8 + (a.binary ? 4 : 0) + (fast ? 2 : 0) + (grad ? 1 : 0)) {
-        case 8: RSF_POINT(false, 1, false, false); break;
-        case 9: RSF_POINT(true, 1, false, false); break;
-        case 10: RSF_POINT(false, 1, false, true); break;
-        case 11: RSF_POINT(true, 1, false, true); break;
-        case 12: RSF_POINT(false, 1, true, false); break;
-        case 13: RSF_POINT(true, 1, true, false); break;
-        case 16: RSF_POINT(false, 2, false, false); break;
-        case 17: RSF_POINT(true, 2, false, false); break;
-        case 18: RSF_POINT(false, 2, false, true); break;
-        case 19: RSF_POINT(true, 2, false, true); break;
-        case 20: RSF_POINT(false, 2, true, false); break;
-        case 21: RSF_POINT(true, 2, true, false); break;
-        case 24: RSF_POINT(false, 3, false, false); break;
-        case 25: RSF_POINT(true, 3, false, false); break;
-        case 26: RSF_POINT(false, 3, false, true); break;
-        case 27: RSF_POINT(true, 3, false, true); break;
-        case 28: RSF_POINT(false, 3, true, false); break;
-        case 29: RSF_POINT(true, 3, true, false); break;
-        default: return hipErrorInvalidValue;
+#define RSF_POINT(K, G, O, B) hipLaunchKernelGGL((K<G, O, B>), grid, dim3(kThreads), 0, s, a)
+#define RSF_POINT_CASES(K)                              \
+    switch (a.order * 4 + (a.binary ? 2 : 0) + (grad ? 1 : 0)) { \
+        case 4: RSF_POINT(K, false, 1, false); break;   \
+        case 5: RSF_POINT(K, true, 1, false); break;    \
+        case 6: RSF_POINT(K, false, 1, true); break;    \
+        case 7: RSF_POINT(K, true, 1, true); break;     \
+        case 8: RSF_POINT(K, false, 2, false); break;   \
+        case 9: RSF_POINT(K, true, 2, false); break;    \
+        case 10: RSF_POINT(K, false, 2, true); break;   \
+        case 11: RSF_POINT(K, true, 2, true); break;    \
+        case 12: RSF_POINT(K, false, 3, false); break;  \
+        case 13: RSF_POINT(K, true, 3, false); break;   \
+        case 14: RSF_POINT(K, false, 3, true); break;   \
+        case 15: RSF_POINT(K, true, 3, true); break;    \
+        default: return hipErrorInvalidValue;           \
     }
+    if (a.run) {
+        RSF_POINT_CASES(rsf_point_run_k)
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || !a.binary) return e;
+    }
+    // a binary plan's candidates choose their kernel on the device, by their orbit
+    RSF_POINT_CASES(rsf_point_k)
+#undef RSF_POINT_CASES
 #undef RSF_POINT
     return hipGetLastError();
 }
 
 hipError_t launch_point_reduce(const PointReduceArgs& r, hipStream_t s) {
     const dim3 grid((unsigned)r.n_cand);
-#define RSF_POINT_REDUCE(O, B) hipLaunchKernelGGL((rsf_point_reduce_k<O, B>), grid, dim3(256), 0, s, r)
+#define RSF_POINT_REDUCE(O, B) hipLaunchKernelGGL((rsf_point_reduce_k<O, B>), grid, dim3(1024), 0, s, r)
     switch (r.order * 2 + (r.binary ? 1 : 0)) {
         case 2: RSF_POINT_REDUCE(1, false); break;
         case 3: RSF_POINT_REDUCE(1, true); break;

@@ -9,11 +9,10 @@
 namespace rsf {
 
 constexpr int kPointSums = 64;      // FP64 partial-sum stride per (block, candidate); at most 58 used
-constexpr int kPointTiles = 8;      // 1024-sample tiles per block
 
 struct PointArgs {
     int64_t n;
-    double dt, t_start, f_het;
+    double dt, inv_dt, t_start, f_het;
     EphDev eph;
     int n_det;
     DetDev det[kMaxDet];
@@ -24,7 +23,8 @@ struct PointArgs {
     const double* theta;      // [n_cand][3 + order (+ 3 when binary)]
     int order;                // spindown order s, 1..3
     int binary;               // theta ends with a circular orbit (a_p, P_b, t_asc)
-    int fast;                 // one detector, no orbit, 63 dt w_sid <= 4e-3: per-run interpolated chain
+    int run;                  // rsf_point_run_k takes the call (binary: the candidates whose orbit it admits)
+    int rows;                 // 64-sample rows per wave (a block: 4 rows)
     int n_cand;
     int64_t P;                // 64-sample rows: ceil(n / 64)
     int n_blocks;             // blocks per candidate
