@@ -193,7 +193,9 @@ int rsf_plan_set_batching(rsf_plan* plan, int fb, int templates);
 int rsf_fft_factor(int64_t n_fft, int lds_bytes, int fft_l1, int32_t* l1, int32_t* l2);
 
 /* Effective batching of rsf_fstat / rsf_fstat_topk for n_sky x n_fdot
- * templates in `mode`: spindowns sharing a first-pass row (*fb), templates
+ * templates in `mode`: spindowns sharing a first-pass row (*fb; with automatic
+ * batching at most that many, fewer in launches too small to fill the device,
+ * with the same results), templates
  * per FFT launch (*templates) and sky positions resampled per launch
  * (*skies).  Host outputs, any may be NULL. */
 int rsf_plan_batching(const rsf_plan* plan, int64_t n_sky, int64_t n_fdot, int mode, int32_t* fb,

@@ -926,9 +926,17 @@ int run_fstat(const rsf_plan* p, const rsf_segment* seg, const double* sky, int6
             A.spin_order = p->spin_order;
             A.nf_l = q.nf;
             A.n_sky_l = q.ns;
-            A.fb = fb;
             A.st = p->stA;
             A.ept = pass_a_ept(p->LA);
+            // spindowns that share a row run one after another in its workgroup:
+            // share fewer where that leaves CUs without their two rounds of
+            // workgroups (1 sky x 16 spindowns, 1350 x 256: 256 workgroups)
+            A.fb = fb;
+            if (p->fb_override == 0) {
+                const int thr = fft_pass_a_threads(A.st, A.P, A.ept, A.LB, p->rowA_fn[0] != nullptr);
+                const int64_t want = 2 * (int64_t)p->n_cu * (kFftThreads / thr);
+                while (A.fb > 1 && (int64_t)A.LB * q.ns * ((q.nf + A.fb - 1) / A.fb) < want) A.fb /= 2;
+            }
             A.tws_lo = p->twA;
             A.tws_hi = p->twA_hi;
             A.tw_lo = p->tw_lo;

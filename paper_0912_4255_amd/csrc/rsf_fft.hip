@@ -625,8 +625,8 @@ struct FixedRow {
     const void* fn[3][2];
 };
 #define RSF_ROW_FN(ORD, ...)                                                 \
-    {(const void*)rsf_fft_pass_a_k<ORD, false, RowPlan<__VA_ARGS__>>,        \
-     (const void*)rsf_fft_pass_a_k<ORD, true, RowPlan<__VA_ARGS__>>}
+    {(const void*)rsf_fft_pass_a_k<ORD, false, RowPlan<__VA_ARGS__>, RowPlan<__VA_ARGS__>::threads()>, \
+     (const void*)rsf_fft_pass_a_k<ORD, true, RowPlan<__VA_ARGS__>, RowPlan<__VA_ARGS__>::threads()>}
 #define RSF_ROW(...)                                                                               \
     {RowPlan<__VA_ARGS__>::kStages, {__VA_ARGS__}, RowPlan<__VA_ARGS__>::tab_entries(),            \
      {RSF_ROW_FN(1, __VA_ARGS__), RSF_ROW_FN(2, __VA_ARGS__), RSF_ROW_FN(3, __VA_ARGS__)}}
@@ -640,14 +640,15 @@ const FixedRow kFixedRows[] = {
 #undef RSF_ROW_FN
 constexpr int kNumFixedRows = (int)(sizeof(kFixedRows) / sizeof(kFixedRows[0]));
 
-// The general-stage kernels [stage capacity: kFftEPT, kFftEPTWide][spindown order - 1][non-temporal spill].
-const void* const kGeneralRows[2][3][2] = {
-    {{(const void*)rsf_fft_pass_a_k<1, false, GeneralStages<kFftEPT>>, (const void*)rsf_fft_pass_a_k<1, true, GeneralStages<kFftEPT>>},
-     {(const void*)rsf_fft_pass_a_k<2, false, GeneralStages<kFftEPT>>, (const void*)rsf_fft_pass_a_k<2, true, GeneralStages<kFftEPT>>},
-     {(const void*)rsf_fft_pass_a_k<3, false, GeneralStages<kFftEPT>>, (const void*)rsf_fft_pass_a_k<3, true, GeneralStages<kFftEPT>>}},
-    {{(const void*)rsf_fft_pass_a_k<1, false, GeneralStages<kFftEPTWide>>, (const void*)rsf_fft_pass_a_k<1, true, GeneralStages<kFftEPTWide>>},
-     {(const void*)rsf_fft_pass_a_k<2, false, GeneralStages<kFftEPTWide>>, (const void*)rsf_fft_pass_a_k<2, true, GeneralStages<kFftEPTWide>>},
-     {(const void*)rsf_fft_pass_a_k<3, false, GeneralStages<kFftEPTWide>>, (const void*)rsf_fft_pass_a_k<3, true, GeneralStages<kFftEPTWide>>}}};
+// The general-stage kernels [threads and stage capacity][spindown order - 1][non-temporal spill].
+#define RSF_GENERAL_FN(ORD, EPT, THR)                                        \
+    {(const void*)rsf_fft_pass_a_k<ORD, false, GeneralStages<EPT>, THR>,     \
+     (const void*)rsf_fft_pass_a_k<ORD, true, GeneralStages<EPT>, THR>}
+#define RSF_GENERAL(EPT, THR) {RSF_GENERAL_FN(1, EPT, THR), RSF_GENERAL_FN(2, EPT, THR), RSF_GENERAL_FN(3, EPT, THR)}
+const void* const kGeneralRows[4][3][2] = {RSF_GENERAL(kFftEPT, 128), RSF_GENERAL(kFftEPT, 256),
+                                           RSF_GENERAL(kFftEPT, kFftThreads), RSF_GENERAL(kFftEPTWide, kFftThreads)};
+#undef RSF_GENERAL
+#undef RSF_GENERAL_FN
 
 // Bytes of LDS of a first-pass row of length LA on the general stages: the
 // row and the two-level stage table.
@@ -668,6 +669,18 @@ int fixed_row_index(const FftStages& st, int64_t P) {
     return -1;
 }
 }  // namespace
+
+namespace {
+int general_row_threads(const FftStages& st, int ept, int LB) {
+    if (ept == kFftEPTWide) return kFftThreads;
+    return row_threads(st.radix, st.n_stages, st.len, kRowPointsGeneral, LB <= kRowsPerDevice ? 256 : 128);
+}
+}  // namespace
+
+int fft_pass_a_threads(const FftStages& st, int64_t P, int ept, int LB, bool run_time) {
+    return run_time || fixed_row_index(st, P) >= 0 ? row_threads(st.radix, st.n_stages, st.len, kRowPointsPlan)
+                                                   : general_row_threads(st, ept, LB);
+}
 
 bool fft_pass_a_fixed(const FftStages& st, int64_t P) { return fixed_row_index(st, P) >= 0; }
 
@@ -692,20 +705,22 @@ hipError_t launch_fft_pass_a(const PassAArgs& a, hipStream_t s, void* const* row
     const unsigned gy = (unsigned)(a.n_sky_l * ((a.nf_l + a.fb - 1) / a.fb));
     const dim3 grid((unsigned)a.LB, gy);
     const int nt = a.nt_spill ? 1 : 0;
+    unsigned thr = (unsigned)row_threads(a.st.radix, a.st.n_stages, a.st.len, kRowPointsPlan);
     void* args[] = {const_cast<PassAArgs*>(&a)};
     // a run-time compiled RowPlan (it prunes the first stage, like the compiled-in ones)
     const size_t lds_row = fft_pass_a_lds(a.LA) + (size_t)row_plan_tab_entries(a.st) * sizeof(float2);
     if (fi < 0 && row_fn && row_fn[nt] && 2 * a.P <= a.LA && a.st.n_stages > 1 && lds_row <= kLdsPerGroupMax)
-        return hipModuleLaunchKernel((hipFunction_t)row_fn[nt], grid.x, grid.y, 1, kNT, 1, 1, (unsigned)lds_row, s,
+        return hipModuleLaunchKernel((hipFunction_t)row_fn[nt], grid.x, grid.y, 1, thr, 1, 1, (unsigned)lds_row, s,
                                      args, nullptr);
     const void* fn;
+    if (fi < 0) thr = (unsigned)general_row_threads(a.st, a.ept, a.LB);
     if (fi >= 0)
         fn = kFixedRows[fi].fn[a.spin_order - 1][nt];
-    else if (a.ept == kFftEPT || a.ept == kFftEPTWide)
-        fn = kGeneralRows[a.ept == kFftEPTWide ? 1 : 0][a.spin_order - 1][nt];
+    else if (a.ept == kFftEPT || (a.ept == kFftEPTWide && thr == kFftThreads))
+        fn = kGeneralRows[a.ept == kFftEPTWide ? 3 : thr == 128 ? 0 : thr == 256 ? 1 : 2][a.spin_order - 1][nt];
     else
         return hipErrorInvalidValue;
-    return hipLaunchKernel(fn, grid, dim3(kNT), args, lds, s);
+    return hipLaunchKernel(fn, grid, dim3(thr), args, lds, s);
 }
 
 // Columns of 64 E points, E = 4, 8, 12, and E = 16 when the pass feeds the

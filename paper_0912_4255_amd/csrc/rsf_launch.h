@@ -23,6 +23,8 @@ int row_plan_tab_entries(const FftStages& st);           // base-twiddle entries
 // (fn[0]: cached spill stores, fn[1]: non-temporal) compiled at run time and
 // loaded on the current device; false (fn null) when that is not available.
 bool row_plan_kernels(int order, const FftStages& plan, void* fn[2]);
+// threads of a first-pass workgroup for rows of plan st (run_time: on a run-time compiled kernel)
+int fft_pass_a_threads(const FftStages& st, int64_t P, int ept, int LB, bool run_time);
 size_t fft_pass_a_lds(int LA);  // general stages
 size_t fft_pass_a_plan_lds(const FftStages& st, int64_t P);  // the kernel a launch of plan st with P rows takes
 hipError_t launch_fft_pass_b(const PassBArgs& b, int n_cu, hipStream_t s);

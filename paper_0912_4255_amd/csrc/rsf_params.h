@@ -50,6 +50,42 @@ struct FftStages {
     int radix[kMaxStages];
 };
 
+// Threads of a first-pass workgroup.  A stage of radix R has len / R
+// butterflies: 512 threads on a 900-point row leave 4 of 5 idle while their
+// registers keep every other workgroup off the CU.  Of 128, 256 and 512, the
+// number that pads the stages to the fewest points, the larger one at a tie;
+// at most `most` points per thread, beyond which the registers spill or the
+// general stages do not hold a radix.  Measured per FFT point with 64
+// templates, 128 / 256 / 512 threads: 4.5 / - / 12.4 ps at 900 points, 4.3 / 5.1 /
+// 8.9 at 1568, 6.3 / 5.2 / 8.7 at 1960 (a tie of the first two), 5.3 / 4.3 / 6.2
+// at 2500, - / 4.6 / 5.3 at 4320, - / 6.4 / 4.8 at 5000 (a tie), - / 9.7 / 6.5 at
+// 5488 (over the limit at 256).  `least`: rows of up to kRowsPerDevice columns
+// (one row per CU for a lone template, whose time is a row's) keep 256: 13.3 us
+// against 15.7 at 128 and 13.9 at 512 for 1350 x 256 points, and 175 against 138
+// and 289 us for 64 templates of them.  Nothing here depends on the launch, so
+// every batching computes the same bits.
+constexpr int kRowPointsPlan = 17, kRowPointsGeneral = 13, kRowsPerDevice = 256;
+constexpr int row_threads(const int* radix, int n_stages, int len, int most, int least = 128) {
+    int best = kFftThreads;
+    long best_padded = 0;
+    for (int thr = kFftThreads; thr >= least; thr /= 2) {
+        if (thr < kFftThreads && len > most * thr) break;
+        long padded = 0;
+        bool fits = true;
+        for (int i = 0; i < n_stages; ++i) {
+            const int b = len / radix[i];
+            padded += (long)((b + thr - 1) / thr) * thr * radix[i];
+            fits = fits && b <= fft_radix_cap(radix[i], thr, kFftEPT);
+        }
+        if (most == kRowPointsGeneral && thr < kFftThreads && !fits) break;
+        if (thr == kFftThreads || padded < best_padded) {
+            best = thr;
+            best_padded = padded;
+        }
+    }
+    return best;
+}
+
 struct EphDev {
     double au_c, re_c, inv_p_orb, inv_p_sid, ceps, seps, lambda0, theta0;
 };

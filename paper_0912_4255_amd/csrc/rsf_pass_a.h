@@ -11,8 +11,6 @@
 
 namespace rsf {
 
-constexpr int kRowThreads = kFftThreads;
-
 // One resampled sample of one detector, unpacked for the integrand: z~,
 // the noise-weighted beam patterns w a, w b, and the spindown coefficients
 // u_j of eq. eq4pt1 in FP64, Phi_s = 2 pi sum_j f^(j) u_j with
@@ -77,9 +75,6 @@ __device__ __forceinline__ void accumulate_integrand(cp& y, const Sample<ORDER>&
     y.w += p.wb * ei;
 }
 
-// Inputs of one row held per thread: n_a = tid + q * kRowThreads, q < kInPer (P <= LA/2 <= 5120).
-constexpr int kInPer = (kFftMaxLen / 2 + kRowThreads - 1) / kRowThreads;
-
 // ---------------------------------------------------------------------------
 // First-pass rows with the radix sequence fixed at compile time (RowPlan<R...>,
 // radices in stage order, the upper half of the row zero).  Stage sizes are
@@ -93,15 +88,15 @@ constexpr int kInPer = (kFftMaxLen / 2 + kRowThreads - 1) / kRowThreads;
 // One middle (or first) stage of length L after Ns points, radix R; table
 // tab = W_{Ns R}^k for k < Ns (unused when Ns = 1).  HZ: the upper half of
 // the input is zero.
-template <int L, int Ns, int R, bool HZ>
+template <int L, int Ns, int R, bool HZ, int THR>
 __device__ __forceinline__ void row_stage(cp* __restrict__ s, const float2* __restrict__ tab) {
     constexpr int LR = L / R;
-    constexpr int MAXB = (LR + kRowThreads - 1) / kRowThreads;
+    constexpr int MAXB = (LR + THR - 1) / THR;
     cp v[MAXB][R];
     const int tid = opaque_tid();
 #pragma unroll
     for (int q = 0; q < MAXB; ++q) {
-        const int j = tid + q * kRowThreads;
+        const int j = tid + q * THR;
         if (q + 1 < MAXB || j < LR) {
 #pragma unroll
             for (int r = 0; r < R; ++r) v[q][r] = (HZ && 2 * r >= R) ? make_float4(0.f, 0.f, 0.f, 0.f) : s[j + r * LR];
@@ -120,7 +115,7 @@ __device__ __forceinline__ void row_stage(cp* __restrict__ s, const float2* __re
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < MAXB; ++q) {
-        const int j = tid + q * kRowThreads;
+        const int j = tid + q * THR;
         if (q + 1 < MAXB || j < LR) {
             const int jq = j / Ns, k = j - jq * Ns;
             cp* p = s + (jq * Ns * R + k);
@@ -133,14 +128,14 @@ __device__ __forceinline__ void row_stage(cp* __restrict__ s, const float2* __re
 
 // The last stage (Ns R = L): butterfly j reads x[j + r Ns], rotates input r
 // by W_L^{j r} and hands its R outputs to the sink, in q order.
-template <int L, int R, typename Sink>
+template <int L, int R, int THR, typename Sink>
 __device__ __forceinline__ void row_last(const cp* __restrict__ s, const TwLds& tw, Sink& sink) {
     constexpr int LR = L / R;
-    constexpr int MAXB = (LR + kRowThreads - 1) / kRowThreads;
+    constexpr int MAXB = (LR + THR - 1) / THR;
     const int tid = opaque_tid();
 #pragma unroll
     for (int q = 0; q < MAXB; ++q) {
-        const int j = tid + q * kRowThreads;
+        const int j = tid + q * THR;
         if (q + 1 < MAXB || j < LR) {
             cp v[R];
 #pragma unroll
@@ -151,16 +146,16 @@ __device__ __forceinline__ void row_last(const cp* __restrict__ s, const TwLds& 
     }
 }
 
-template <int L, int Ns, bool HZ, int R, int... Rest>
+template <int L, int Ns, bool HZ, int THR, int R, int... Rest>
 struct RowStages {
     template <typename Sink>
     __device__ __forceinline__ static void run(cp* __restrict__ s, const float2* __restrict__ tab, const TwLds& tw,
                                                Sink& sink) {
         if constexpr (sizeof...(Rest) == 0) {
-            row_last<L, R>(s, tw, sink);
+            row_last<L, R, THR>(s, tw, sink);
         } else {
-            row_stage<L, Ns, R, HZ>(s, tab);
-            RowStages<L, Ns * R, false, Rest...>::run(s, Ns > 1 ? tab + Ns : tab, tw, sink);
+            row_stage<L, Ns, R, HZ, THR>(s, tab);
+            RowStages<L, Ns * R, false, THR, Rest...>::run(s, Ns > 1 ? tab + Ns : tab, tw, sink);
         }
     }
 };
@@ -169,6 +164,10 @@ template <int... R>
 struct RowPlan {
     static constexpr int kStages = sizeof...(R);
     static constexpr int kLen = (R * ...);
+    static constexpr int threads() {
+        constexpr int r[] = {R...};
+        return row_threads(r, kStages, kLen, kRowPointsPlan);
+    }
     // entries of the middle stages' base-twiddle tables (Ns of each)
     static constexpr int tab_entries() {
         constexpr int r[] = {R...};
@@ -181,21 +180,22 @@ struct RowPlan {
     }
     // table of middle stage i (Ns = r_0 .. r_(i-1)): W_{Ns r_i}^k, k < Ns,
     // from the two-level table
+    template <int THR>
     __device__ __forceinline__ static void tables(float2* tab, const TwLds& tw) {
         constexpr int r[] = {R...};
         int off = 0, ns = r[0];
 #pragma unroll
         for (int i = 1; i + 1 < kStages; ++i) {
             const int step = kLen / (ns * r[i]);
-            for (int k = threadIdx.x; k < ns; k += kRowThreads) tab[off + k] = tw(k * step);
+            for (int k = threadIdx.x; k < ns; k += THR) tab[off + k] = tw(k * step);
             off += ns;
             ns *= r[i];
         }
     }
-    template <typename Sink>
+    template <int THR, typename Sink>
     __device__ __forceinline__ static void fft(cp* __restrict__ s, const float2* __restrict__ tab, const TwLds& tw,
                                                Sink& sink) {
-        RowStages<kLen, 1, true, R...>::run(s, tab, tw, sink);
+        RowStages<kLen, 1, true, THR, R...>::run(s, tab, tw, sink);
     }
 };
 
@@ -208,28 +208,34 @@ struct GeneralStages {
 template <typename T>
 struct IsRowPlan {
     static constexpr bool value = false;
+    // longest row of a workgroup of THR threads
+    static constexpr int max_len(int THR) { return THR < kFftThreads ? kRowPointsGeneral * THR : kFftMaxLen; }
 };
 template <int... R>
 struct IsRowPlan<RowPlan<R...>> {
     static constexpr bool value = true;
+    static constexpr int max_len(int) { return RowPlan<R...>::kLen; }
 };
 
 // NT: the launch's spill is larger than the last-level cache (non-temporal stores)
 // PLAN: a fixed row plan (RowPlan), or the planned stages of A.st
 // (GeneralStages with kFftEPT or kFftEPTWide complex pairs per thread).
-template <int ORDER, bool NT, typename PLAN>
-__global__ __launch_bounds__(kRowThreads) void rsf_fft_pass_a_k(PassAArgs A) {
+// THR: threads of the workgroup (row_threads).
+template <int ORDER, bool NT, typename PLAN, int THR>
+__global__ __launch_bounds__(THR, 2) void rsf_fft_pass_a_k(PassAArgs A) {
+    // inputs of the row held per thread: n_a = tid + q THR, q < kInPer (P <= ceil(LA / 2))
+    constexpr int kInPer = ((IsRowPlan<PLAN>::max_len(THR) + 1) / 2 + THR - 1) / THR;
     extern __shared__ float4 lds[];
     // stage twiddles in LDS after the row: no global load inside the stages,
     // so the spill stores of one spindown stay in flight during the next FFT
     float2* twl = reinterpret_cast<float2*>(lds + A.LA);
     const int n_hi = (A.LA + 31) >> kTwLoBits;
-    for (int i = threadIdx.x; i < 32 + n_hi; i += kRowThreads) twl[i] = (i < 32) ? A.tws_lo[i] : A.tws_hi[i - 32];
+    for (int i = threadIdx.x; i < 32 + n_hi; i += THR) twl[i] = (i < 32) ? A.tws_lo[i] : A.tws_hi[i - 32];
     const TwLds tws{twl, twl + 32};
     float2* tab = twl + 32 + n_hi;
     if constexpr (IsRowPlan<PLAN>::value) {
         __syncthreads();  // the two-level table is complete
-        PLAN::tables(tab, tws);
+        PLAN::template tables<THR>(tab, tws);
     }
     const int n_b = blockIdx.x;
     const int gpf = (A.nf_l + A.fb - 1) / A.fb;       // spindown groups per sky
@@ -245,7 +251,7 @@ __global__ __launch_bounds__(kRowThreads) void rsf_fft_pass_a_k(PassAArgs A) {
     float tm0[kInPer];
 #pragma unroll
     for (int q = 0; q < kInPer; ++q) {
-        const int n_a = tid + q * kRowThreads;
+        const int n_a = tid + q * THR;
         const int64_t k = (int64_t)A.LB * n_a + n_b;
         if (n_a < A.P && k < A.n) {
             m0[q] = A.rs_main[0][row + n_a];
@@ -258,7 +264,7 @@ __global__ __launch_bounds__(kRowThreads) void rsf_fft_pass_a_k(PassAArgs A) {
     Sample<ORDER> p0[kInPer];
 #pragma unroll
     for (int q = 0; q < kInPer; ++q) {
-        const int64_t k = (int64_t)A.LB * (tid + q * kRowThreads) + n_b;
+        const int64_t k = (int64_t)A.LB * (tid + q * THR) + n_b;
         p0[q] = unpack_sample<ORDER>(m0[q], tm0[q], A.f16, (double)k * A.dt, (float)A.w[0]);
     }
     // the upper half of the row is zero padding when P <= LA/2: the pruned
@@ -267,9 +273,9 @@ __global__ __launch_bounds__(kRowThreads) void rsf_fft_pass_a_k(PassAArgs A) {
     const bool prune = 2 * A.P <= A.LA && A.st.n_stages > 1;
     const int zlim = prune ? pruned_first_reach(A.LA, A.st.radix[0]) : A.LA;
 
-    // inter-pass twiddle W_N^{n_b k_a} for k_a = tid + q kRowThreads: base W^{n_b tid}, step W^{n_b kRowThreads}
+    // inter-pass twiddle W_N^{n_b k_a} for k_a = tid + q THR: base W^{n_b tid}, step W^{n_b THR}
     const int64_t mb = ((int64_t)n_b * tid) % A.n_fft;
-    const int64_t ms = ((int64_t)n_b * kRowThreads) % A.n_fft;
+    const int64_t ms = ((int64_t)n_b * THR) % A.n_fft;
     const int msk = (1 << kTwSplitBits) - 1;
     const float2 w_base = c_mul(A.tw_hi[mb >> kTwSplitBits], A.tw_lo[mb & msk]);
     const float2 w_step = c_mul(A.tw_hi[ms >> kTwSplitBits], A.tw_lo[ms & msk]);
@@ -291,7 +297,7 @@ __global__ __launch_bounds__(kRowThreads) void rsf_fft_pass_a_k(PassAArgs A) {
         for (int j = 0; j < ORDER; ++j) fd.f[j] = fdot_c[(int64_t)f * ORDER + j];
 #pragma unroll
         for (int q = 0; q < kInPer; ++q) {
-            const int n_a = tid + q * kRowThreads;
+            const int n_a = tid + q * THR;
             if (n_a < zlim) {
                 cp y = make_float4(0.f, 0.f, 0.f, 0.f);
                 const int64_t k = (int64_t)A.LB * n_a + n_b;
@@ -307,14 +313,14 @@ __global__ __launch_bounds__(kRowThreads) void rsf_fft_pass_a_k(PassAArgs A) {
                 lds[n_a] = y;
             }
         }
-        for (int n_a = tid + kInPer * kRowThreads; n_a < zlim; n_a += kRowThreads) lds[n_a] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int n_a = tid + kInPer * THR; n_a < zlim; n_a += THR) lds[n_a] = make_float4(0.f, 0.f, 0.f, 0.f);
         __syncthreads();
         SpillSink<NT> sink{reinterpret_cast<char*>(A.spill + (int64_t)t * A.spill_tmpl_stride), A.LB, n_b, lr,
                            w_base, w_step, w_lr};
         if constexpr (IsRowPlan<PLAN>::value)
-            PLAN::fft(lds, tab, tws, sink);
+            PLAN::template fft<THR>(lds, tab, tws, sink);
         else
-            lds_fft_into<kRowThreads, PLAN::kFftEPT, 1, false>(lds, A.st, tws, Interleaved<1>{}, sink, NoMid{}, prune);
+            lds_fft_into<THR, PLAN::kFftEPT, 1, false>(lds, A.st, tws, Interleaved<1>{}, sink, NoMid{}, prune);
         __syncthreads();
     }
 }

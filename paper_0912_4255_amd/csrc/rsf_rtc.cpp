@@ -194,7 +194,7 @@ bool row_plan_kernels(int order, const FftStages& plan, void* fn[2]) {
     std::string exprs[2];
     for (int nt = 0; nt < 2; ++nt)
         exprs[nt] = "rsf::rsf_fft_pass_a_k<" + std::to_string(order) + ", " + (nt ? "true" : "false") +
-                    ", rsf::RowPlan<" + radices + ">>";
+                    ", rsf::RowPlan<" + radices + ">, " + std::to_string(row_threads(plan.radix, plan.n_stages, plan.len, kRowPointsPlan)) + ">";
     const std::string key = std::to_string(device) + ":" + exprs[0];
     std::lock_guard<std::mutex> lock(g_mu);
     Loaded& e = g_loaded[key];
