@@ -68,13 +68,13 @@ def parse():
 
 
 KERNEL_SOURCES = ("rsf_fft.hip", "rsf_pass_a.h", "rsf_spill.h", "rsf_topk_gate.h", "rsf_device.h", "rsf_params.h",
-                  "rsf_resample.hip")
+                  "rsf_resample.hip", "rsf_chain.h")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pmc_traffic_fft_T10d.md")
 PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X dense FP32 matrix
 # Vector-instruction issue: 256 CUs x 4 SIMDs, one wave64 VALU instruction per
 # SIMD every 4 cycles at 2.4 GHz (FP64 and unpacked FP32 alike).
 PEAK_VALU_ISSUE_G = 256 * 4 * 2.4 / 4  # 614.4 G wave instructions/s
-POINT_SOURCES = ("rsf_point.hip", "rsf_point_params.h", "rsf_device.h", "rsf_params.h")
+POINT_SOURCES = ("rsf_point.hip", "rsf_chain.h", "rsf_point_params.h", "rsf_device.h", "rsf_params.h")
 POINT_COUNTS_FILE = os.path.join(ROOT, "profiles", "pmc_point_grad_T10d.md")
 
 

@@ -386,6 +386,9 @@ WsLayout fstat_layout(const rsf_plan* p, int64_t n_sky, int64_t n_fdot, int mode
     return L;
 }
 
+// natural order as rows of this many samples (a multiple of 32: whole mask words)
+constexpr int kNaturalRow = 128;
+
 struct ResLayout {
     size_t flags, partials, coef, total;
     int n_blocks;
@@ -396,8 +399,8 @@ ResLayout resample_layout(const rsf_plan* p, int64_t n_sky) {
     size_t off = 0;
     L.flags = off;
     off = align_up(off + 64);
-    const int64_t P = (p->n + 63) / 64;
-    L.n_blocks = resample_blocks(64, P);
+    const int64_t P = (p->n + kNaturalRow - 1) / kNaturalRow;
+    L.n_blocks = resample_blocks(kNaturalRow, P);
     L.partials = off;
     off = align_up(off + (size_t)p->d.n_det * n_sky * L.n_blocks * 3 * sizeof(double));
     L.coef = off;
@@ -447,7 +450,7 @@ ResampleArgs base_resample_args(const rsf_plan* p, const rsf_segment* seg, int X
     a.x = (const float2*)seg->x[X];
     a.gaps = seg->gaps[X];
     a.n_gaps = seg->n_gaps[X];
-    a.fast_chain = (!p->binary && 63.0 * p->d.dt * 2.0 * M_PI * std::fabs(p->eph.inv_p_sid) <= 4e-3) ? 1 : 0;
+    a.run = resample_interpolates(p->d.dt, p->eph) ? 1 : 0;
     return a;
 }
 
@@ -754,13 +757,13 @@ int rsf_resample(const rsf_plan* p, const rsf_segment* seg, const double* sky, i
     char* w = (char*)ws;
     unsigned int* flags = (unsigned int*)(w + L.flags);
     RSF_HIP(launch_fill_u32(flags, 16, 0u, s), "flags clear");
-    const int64_t P = (p->n + 63) / 64;
+    const int64_t P = (p->n + kNaturalRow - 1) / kNaturalRow;
     for (int X = 0; X < p->d.n_det; ++X) {
         ResampleArgs a = base_resample_args(p, seg, X);
         a.sky = sky;
         a.sky_stride = p->binary ? 5 : 2;
         a.binary = p->binary;
-        a.LB = 64;
+        a.LB = kNaturalRow;
         a.P = P;
         a.layout = 0;
         if (p->d.storage == RSF_STORE_F16) {

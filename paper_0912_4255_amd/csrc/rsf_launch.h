@@ -12,6 +12,7 @@ namespace rsf {
 
 hipError_t launch_resample(const ResampleArgs& a, int n_sky, hipStream_t s);
 int resample_blocks(int LB, int64_t P);
+bool resample_interpolates(double dt, const EphDev& e);  // the interpolated timing chain holds at this sampling interval
 hipError_t launch_antenna_reduce(const ReduceArgs& r, hipStream_t s);
 
 // row_fn: a run-time compiled RowPlan kernel of a.st per non-temporal flag

@@ -33,7 +33,7 @@
 // forms 2F (eq. eq6) and the vector-Jacobian product g * d2F/dtheta.
 #include <climits>
 
-#include "rsf_device.h"
+#include "rsf_chain.h"
 #include "rsf_launch.h"
 
 namespace rsf {
@@ -42,7 +42,6 @@ namespace {
 constexpr int kTileB = 64;
 constexpr int kThreads = 256;
 constexpr int kWinMax = kTileB + kMaxTaps + 8;
-constexpr float kPiF = 3.14159265358979323846f;
 
 // partial-sum slots at spindown order ORDER: NP = 1 + ORDER + NS parameters,
 // the last NS of which (alpha, delta, and a_p, P_b, t_asc for a binary
@@ -193,34 +192,6 @@ __device__ __forceinline__ RoemerD project(const Orbit& o, double3 m, const EphD
 }
 
 
-
-__device__ __forceinline__ bool in_gap(const int64_t* __restrict__ gaps, int n_gaps, int64_t j) {
-    int lo = 0, hi = n_gaps - 1, best = -1;
-    while (lo <= hi) {
-        const int mid = (lo + hi) >> 1;
-        if (gaps[2 * mid] <= j) {
-            best = mid;
-            lo = mid + 1;
-        } else {
-            hi = mid - 1;
-        }
-    }
-    return best >= 0 && j < gaps[2 * best + 1];
-}
-
-// sinc(x) = sin(pi x)/(pi x) and its derivative from accurate sin(pi x), cos(pi x);
-// a series near 0 avoids the cancellation in (cos(pi x) - sinc(x)) / x.
-__device__ __forceinline__ void sinc_d(float x, float sx, float cx, float& s, float& ds) {
-    if (fabsf(x) < 0.05f) {
-        const float p2 = kPiF * kPiF * x * x;
-        s = 1.f - p2 / 6.f + p2 * p2 / 120.f - p2 * p2 * p2 / 5040.f;
-        ds = -(kPiF * kPiF * x / 3.f) * (1.f - p2 / 10.f + p2 * p2 / 280.f);
-    } else {
-        const float rx = __builtin_amdgcn_rcpf(x);
-        s = sx * rx * (1.f / kPiF);
-        ds = (cx - s) * rx;
-    }
-}
 
 // Interpolation weight w(x) and w'(x) (Lanczos-W or the periodic Dirichlet
 // kernel of length n written as sinc(x) g(pi x / n)); sx, cx = sin/cos(pi x).
@@ -401,30 +372,20 @@ __device__ __forceinline__ double wave_sums(const double (&acc)[V], int lane) {
     return v[0];
 }
 
-// Interpolated timing chain.  Runs of 256 consecutive resampled samples
-// (four rows of 64) take every slowly varying quantity (the delay d, the beam
-// patterns and, for the gradient, dT/dtheta and the patterns' derivatives)
-// from the quartic through five exact nodes, at s = -138.5, -85.5, 0, 85.5 and
-// 138.5 samples from the run's centre (near the Chebyshev points of the run and
-// the window around it, |s| <= kRunHalf).  Each quantity is a sum of circular
-// motions, so with rate w and H = kRunHalf dt the remainder is at most
-// A (w H)^5 / 1920, A the amplitude; the host admits sampling intervals for
-// which that is at most 1e-11 s for t_m and 4e-9 for a and b (2 w_sid), i.e.
-// dt up to 4.4 s, and orbit_interpolates() the orbits for which it is at
-// most 1e-11 s for R and 3e-11 relative for its derivatives.
-constexpr int kRunRows = 4;                      // rows of 64 samples per run
+// The point search's runs: 256 samples (four rows of 64).
+constexpr int kRunRows = 4;
 constexpr int kRunLen = kRunRows * kTileB;
-constexpr double kRunMid = 0.5 * (kRunLen - 1);  // the centre's index in the run
-constexpr double kRunHalf = 146.0;               // samples from the centre that are interpolated
-constexpr double kNodeP = 138.5, kNodeQ = 85.5;
-constexpr int kRunsMax = 8 * 4;                  // runs of a workgroup
+struct PointRun {
+    static constexpr double mid = 0.5 * (kRunLen - 1), half = 146.0, p = 138.5, q = 85.5;
+};
+constexpr double kRunMid = PointRun::mid;
+constexpr int kRunsMax = 8 * 4;  // runs of a workgroup
 // window of a run's rows: 64 samples and their compression (104 - W slots a
 // row, as the general kernel stages), and the taps
 constexpr int kRunWin = 416;
 
 __device__ __forceinline__ bool orbit_interpolates(const BinaryOrbit& b, double dt) {
-    const double x = 2.0 * kPi / b.p_orb * kRunHalf * dt;
-    return x <= 0.035 && b.a_p * (x * x) * (x * x) * x <= 1e-11 * 1920.0;
+    return orbit_slow(b, PointRun::half * dt);
 }
 
 // Per run: quartics in s of the NQ quantities V = d / dt, a, b (and, for the
@@ -439,47 +400,8 @@ struct RunVals {
     double G[3];                     // 1 / (1 - V'(s)) to second order
     double psi[GRAD ? NS : 1][3];    // see rsf_point_run_k
     double vn[5];                    // V at the nodes
-    int gap, pad;                    // 0: no sample of the run near a gap, 1: all inside one, 2: look
+    int gap, pad;                    // gap_state of the run
 };
-
-__device__ __forceinline__ double quartic(const double* c, double s) {
-    return c[0] + s * (c[1] + s * (c[2] + s * (c[3] + s * c[4])));
-}
-
-// node values at -p, -q, 0, q, p to the quartic's coefficients
-__device__ __forceinline__ void to_quartic(double* c) {
-    constexpr double p = kNodeP, q = kNodeQ, ip2 = 1.0 / (p * p), iq2 = 1.0 / (q * q), idiff = 1.0 / (p * p - q * q);
-    const double f0 = c[2];
-    const double ep = (0.5 * (c[4] + c[0]) - f0) * ip2, eq = (0.5 * (c[3] + c[1]) - f0) * iq2;
-    const double op = 0.5 * (c[4] - c[0]) * (1.0 / p), oq = 0.5 * (c[3] - c[1]) * (1.0 / q);
-    const double c4 = (ep - eq) * idiff, c3 = (op - oq) * idiff;
-    c[0] = f0;
-    c[1] = op - c3 * (p * p);
-    c[2] = ep - c4 * (p * p);
-    c[3] = c3;
-    c[4] = c4;
-}
-
-// the quartic through (x[i], y[i]) about x = 0, by divided differences; the
-// x[i] are near -p, -q, 0, q, p
-__device__ __forceinline__ void through(const double* x, const double* y, double* out) {
-    double c[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) c[i] = y[i];
-#pragma unroll
-    for (int k = 1; k < 5; ++k)
-#pragma unroll
-        for (int i = 4; i >= k; --i) c[i] = (c[i] - c[i - 1]) / (x[i] - x[i - k]);
-    double m[5] = {c[4], 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int k = 3; k >= 0; --k) {
-#pragma unroll
-        for (int i = 4 - k; i > 0; --i) m[i] = m[i - 1] - x[k] * m[i];
-        m[0] = c[k] - x[k] * m[0];
-    }
-#pragma unroll
-    for (int i = 0; i < 5; ++i) out[i] = m[i];
-}
 
 // The binary gradient's 50 to 58 FP64 partial sums do not fit beside the rest
 // at two waves per SIMD; at one wave per SIMD its spills go to the
@@ -934,7 +856,7 @@ __global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 2 : (GRAD ? 3 : 4)) void 
             geo.pa = make_double3(-ca, -sa, 0.0);
             geo.qa = make_double3(sd * sa, -sd * ca, 0.0);
             geo.qd = make_double3(-cd * ca, -cd * sa, -sd);
-            const double s = i == 0 ? -kNodeP : i == 1 ? -kNodeQ : i == 2 ? 0.0 : i == 3 ? kNodeQ : kNodeP;
+            const double s = node_at<PointRun>(i);
             const double tb = ((double)((row_b + (int64_t)rr * kRunRows) * kTileB) + (kRunMid + s)) * A.dt;
             const double tau = A.t_start + tb;
             RunAngles ra;
@@ -971,17 +893,10 @@ __global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 2 : (GRAD ? 3 : 4)) void 
             const int rr = e / (NQ + 1), qi = e - rr * (NQ + 1);
             RV& v = runs[rr];
             if (qi < NQ) {
-                to_quartic(v.poly[qi]);
+                to_quartic<PointRun>(v.poly[qi]);
             } else {
-                double x[5], y[5];
                 const double uc = (double)((row_b + (int64_t)rr * kRunRows) * kTileB) + kRunMid - v.vn[2];
-                const double at[5] = {-kNodeP, -kNodeQ, 0.0, kNodeQ, kNodeP};
-#pragma unroll
-                for (int i = 0; i < 5; ++i) {
-                    x[i] = at[i] - (v.vn[i] - v.vn[2]);
-                    y[i] = A.f_het * (v.vn[i] * A.dt);
-                }
-                through(x, y, v.het);
+                window_delay<PointRun>(v.vn, A.f_het * A.dt, v.het);
                 v.u_c = uc;
             }
         }
@@ -1010,23 +925,7 @@ __global__ __launch_bounds__(kThreads, (BIN && GRAD) ? 2 : (GRAD ? 3 : 4)) void 
             const double k0 = (double)((row_b + (int64_t)tid * kRunRows) * kTileB);
             const int64_t lo = (int64_t)floor(k0 - quartic(V, -kRunMid)) - 2;
             const int64_t hi = (int64_t)floor(k0 + (kRunLen - 1) - quartic(V, kRunMid)) + 3;
-            const int64_t* gaps = A.gaps[X];
-            int b = -1;  // last gap that starts at or before hi
-            for (int l = 0, h = A.n_gaps[X] - 1; l <= h;) {
-                const int mid = (l + h) >> 1;
-                if (gaps[2 * mid] <= hi) {
-                    b = mid;
-                    l = mid + 1;
-                } else {
-                    h = mid - 1;
-                }
-            }
-            int state = 0;
-            if (b >= 0) {
-                const int64_t s0 = gaps[2 * b], e0 = gaps[2 * b + 1];
-                state = e0 <= lo ? 0 : (s0 <= lo && e0 > hi) ? 1 : 2;
-            }
-            v.gap = state;
+            v.gap = gap_state(A.gaps[X], A.n_gaps[X], lo, hi);
         }
         __syncthreads();
 
@@ -1357,12 +1256,8 @@ __global__ __launch_bounds__(1024) void rsf_point_reduce_k(PointReduceArgs R) {
 int point_rows(int64_t P) { return P <= 512 ? 1 : P <= 4096 ? 4 : P <= 8192 ? 8 : P <= 16384 ? 16 : 32; }
 int point_blocks(int64_t P, int rows) { return (int)((P + 4 * rows - 1) / (4 * rows)); }
 
-bool point_interpolates(double dt, const EphDev& e) {
-    const double H = kRunHalf * dt;
-    const double xo = 2.0 * kPi * fabs(e.inv_p_orb) * H, xs = 2.0 * kPi * fabs(e.inv_p_sid) * H;
-    auto p5 = [](double x) { return x * x * x * x * x / 1920.0; };
-    return fabs(e.au_c) * p5(xo) + fabs(e.re_c) * p5(xs) <= 1e-11 && p5(2.0 * xs) <= 4e-9 && xo <= 0.1;
-}
+// sampling intervals up to 4.4 s
+bool point_interpolates(double dt, const EphDev& e) { return chain_interpolates(e, PointRun::half * dt, 4e-9); }
 
 hipError_t launch_point(const PointArgs& a, bool grad, hipStream_t s) {
     const dim3 grid((unsigned)a.n_blocks, (unsigned)a.n_cand);
