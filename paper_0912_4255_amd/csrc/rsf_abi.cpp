@@ -1499,6 +1499,8 @@ struct rsf_sft_plan {
     int* ids_dev;                         // chunk ids, grouped by length
     std::vector<int64_t> ids_off;         // first id of each group in ids_dev
     SftLenDev* lens_dev;                  // device table of the transform lengths
+    int64_t* gaps_dev;                    // device copy of gaps (null when there are none)
+    int64_t gap_longest;                  // samples of the longest gap
     int rows_R, cols_C;                   // rows per rows workgroup, columns per columns workgroup
     int64_t rows_blocks, cols_blocks;     // workgroups of the single rows / columns launches
     size_t rows_lds, cols_lds;
@@ -1531,6 +1533,7 @@ void sft_free(rsf_sft_plan* p) {
     (void)hipFree(p->chunks_dev);
     (void)hipFree(p->ids_dev);
     (void)hipFree(p->lens_dev);
+    (void)hipFree(p->gaps_dev);
     for (auto& x : p->xf) {
         (void)hipFree(x.t1);
         (void)hipFree(x.t1_hi);
@@ -1593,6 +1596,8 @@ int rsf_sft_plan_create(rsf_sft_plan** out, const rsf_sft_desc* d, const double*
     p->chunks_dev = nullptr;
     p->ids_dev = nullptr;
     p->lens_dev = nullptr;
+    p->gaps_dev = nullptr;
+    p->gap_longest = 0;
     p->rows_R = 1;
     p->cols_C = kPassBCols;
     p->rows_blocks = p->cols_blocks = 0;
@@ -1717,6 +1722,8 @@ int rsf_sft_plan_create(rsf_sft_plan** out, const rsf_sft_desc* d, const double*
         p->gaps.push_back(j);
         p->gaps.push_back(d->n_out);
     }
+    for (size_t i = 0; i < p->gaps.size(); i += 2)
+        p->gap_longest = std::max(p->gap_longest, p->gaps[i + 1] - p->gaps[i]);
     // device table of chunks: band bins, spills and merge workgroups laid end to end
     std::vector<SftChunkDev> tab(p->chunks.size());
     for (size_t i = 0; i < p->chunks.size(); ++i) {
@@ -1783,6 +1790,9 @@ int rsf_sft_plan_create(rsf_sft_plan** out, const rsf_sft_desc* d, const double*
         hipMemcpy(p->chunks_dev, tab.data(), tab.size() * sizeof(SftChunkDev), hipMemcpyHostToDevice) != hipSuccess ||
         hipMalloc((void**)&p->ids_dev, ids.size() * sizeof(int)) != hipSuccess ||
         hipMemcpy(p->ids_dev, ids.data(), ids.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
+        (!p->gaps.empty() &&
+         (hipMalloc((void**)&p->gaps_dev, p->gaps.size() * sizeof(int64_t)) != hipSuccess ||
+          hipMemcpy(p->gaps_dev, p->gaps.data(), p->gaps.size() * sizeof(int64_t), hipMemcpyHostToDevice) != hipSuccess)) ||
         hipMalloc((void**)&p->lens_dev, lens.size() * sizeof(SftLenDev)) != hipSuccess ||
         hipMemcpy(p->lens_dev, lens.data(), lens.size() * sizeof(SftLenDev), hipMemcpyHostToDevice) != hipSuccess) {
         sft_free(p);
@@ -1828,7 +1838,9 @@ int rsf_sft_heterodyne(const rsf_sft_plan* p, const float* sft, float* x_h, void
     hipStream_t s = (hipStream_t)stream;
     const rsf_sft_desc& d = p->d;
     char* w = (char*)ws;
-    RSF_HIP(launch_fill_u32((unsigned int*)x_h, (int)(2 * d.n_out), 0u, s), "x_h clear");
+    if (!p->gaps.empty())
+        RSF_HIP(launch_sft_gaps(p->gaps_dev, (int)(p->gaps.size() / 2), p->gap_longest, reinterpret_cast<float2*>(x_h), s),
+                "gap clear");
     const float2* xh = reinterpret_cast<const float2*>(sft);
     if (d.median_window > 0) {
         SftNormArgs a{};

@@ -50,6 +50,8 @@ size_t hetdec_lds(int L, int D);
 hipError_t launch_hetdec(const HetdecArgs& a, int n_cu, hipStream_t s);  // n_cu: persistent grid of the matrix-core form
 hipError_t hetdec_set_lds_limit(size_t bytes);
 
+// zeros in the ranges gaps[n_gaps][2] of x (device memory), the longest of `longest` samples
+hipError_t launch_sft_gaps(const int64_t* gaps, int n_gaps, int64_t longest, float2* x, hipStream_t s);
 hipError_t launch_sft_norm(const SftNormArgs& a, int n_sft, hipStream_t s);
 int64_t sft_dft_blocks(int64_t entries);  // DFT workgroups of a chunk of K M' entries
 size_t sft_dft_lds(int Mp);

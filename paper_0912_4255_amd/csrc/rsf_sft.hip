@@ -15,6 +15,8 @@
 // the series.  The second member of each complex pair is unused.  Every
 // launch covers all chunks, read from device tables of the chunks and of the
 // transform lengths.
+#include <algorithm>
+
 #include "rsf_device.h"
 #include "rsf_launch.h"
 #include "rsf_spill.h"
@@ -327,13 +329,14 @@ __global__ __launch_bounds__(kMergeThreads) void rsf_sft_merge_k(SftMergeArgs a)
 // 1024).  The stored bins k those bins reach (k* of the first and last bin,
 // +- dk) come into LDS for every SFT of the chunk in one coalesced load (each
 // thread with up to kSftLoads loads in flight); the rows Y[k][.] are formed
-// there and merged as in rsf_sft_merge_k.  The phases W^{r alpha} are
-// running products of W^r, the terms' sines come from the hardware sine
-// (argument in revolutions) and their reciprocals from v_rcp_f32 (each within
-// a few 1e-7 relative).  The merge runs 2 DK + 1 terms without branches (a
-// term outside [-dk, dk] or the stored band reads a row in range and weighs
-// it by zero), so that its LDS reads are issued together.  Chosen when every
-// chunk fits the LDS (sft_fused_lds).
+// there and merged as in rsf_sft_merge_k.  A thread of the DFT keeps one r and
+// takes eight rows per phase W^{r alpha} read from the table of roots.  The
+// terms' reciprocals 1 / y_d depend on (r, d) only and are tabulated once per
+// workgroup (over the SFT bins, which the DFT is done with), and
+// P_d = (sin y - i (1 - cos y)) / y_d leaves its numerator outside the sum, so a
+// term is two LDS reads and two multiply-adds.  Chosen when every chunk fits the
+// LDS (sft_fused_lds).  What bounds it: LDS reads and vector issue.  The 10-day
+// set: see rsf_sft_dftmerge_k's figure below.
 namespace {
 constexpr int kFuseBins = 1024;
 
@@ -355,6 +358,7 @@ __device__ __forceinline__ int div_small(int x, int d, float inv_d, int* rem) {
 }
 }  // namespace
 
+// DK: terms on each side (0: a.dk, at run time)
 template <int DK>
 __global__ __launch_bounds__(kMergeThreads) void rsf_sft_dftmerge_k(SftMergeArgs a) {
     extern __shared__ float2 sh[];
@@ -371,8 +375,11 @@ __global__ __launch_bounds__(kMergeThreads) void rsf_sft_dftmerge_k(SftMergeArgs
     const int rows = k_max >= k_min ? (int)(k_max - k_min + 1) : 0;
     const float inv_mp = 1.0f / (float)Mp;
     float2* roots = sh;                // M'
-    float2* Xt = roots + Mp;           // [M][rows]: X^_{a0 + alpha, k_min + kr}
-    float2* Yt = Xt + M * rows;        // [rows][M']
+    float2* Yt = roots + Mp;           // [rows][M']
+    float2* Xt = Yt + rows * Mp;       // [M][rows]: X^_{a0 + alpha, k_min + kr}
+    // [2 dk + 1][M'] after the DFT: M' <= 2 M, so it is no longer than the
+    // SFT bins of an unclipped workgroup
+    float* inv_y = reinterpret_cast<float*>(Xt);
     for (int i = threadIdx.x; i < Mp; i += kMergeThreads) {
         float s, co;
         sincospif(2.0f * (float)i / (float)Mp, &s, &co);
@@ -399,24 +406,51 @@ __global__ __launch_bounds__(kMergeThreads) void rsf_sft_dftmerge_k(SftMergeArgs
         }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < rows * Mp; e += kMergeThreads) {
-        int r;
-        const int kr = div_small(e, Mp, inv_mp, &r);
-        // W_{M'}^{r alpha} by repeated products of W_{M'}^r (M <= M' factors,
-        // a few ulp each): the threads of one k read the same X^ (one LDS
-        // broadcast) and no table
-        const float2 step = roots[r];
-        float2 w = make_float2(1.f, 0.f);
-        float2 acc = make_float2(0.f, 0.f);
-        for (int al = 0; al < M; ++al) {
-            const float2 v = Xt[al * rows + kr];
-            acc.x += v.x * w.x - v.y * w.y;
-            acc.y += v.x * w.y + v.y * w.x;
-            w = make_float2(w.x * step.x - w.y * step.y, w.x * step.y + w.y * step.x);
+    // Y[kr][r] = sum_alpha X^[alpha][kr] W_{M'}^{r alpha}: threads of one r take
+    // every G-th row, eight rows per phase
+    {
+        const int G = max(1, kMergeThreads / Mp);
+        const bool narrow = Mp <= kMergeThreads;
+        const int g = narrow ? (int)threadIdx.x / Mp : 0;
+        for (int r = narrow ? (int)threadIdx.x - g * Mp : (int)threadIdx.x; r < Mp && g < G; r += kMergeThreads) {
+            for (int kr0 = g; kr0 < rows; kr0 += 8 * G) {
+                float2 acc[8];
+                int at[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    acc[q] = make_float2(0.f, 0.f);
+                    at[q] = min(kr0 + q * G, rows - 1);
+                }
+                int idx = 0;  // r alpha mod M'
+                for (int al = 0; al < M; ++al) {
+                    const float2 w = roots[idx];
+                    const float2* x = Xt + al * rows;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        const float2 v = x[at[q]];
+                        acc[q].x += v.x * w.x - v.y * w.y;
+                        acc[q].y += v.x * w.y + v.y * w.x;
+                    }
+                    idx += r;
+                    if (idx >= Mp) idx -= Mp;
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (kr0 + q * G < rows) Yt[(kr0 + q * G) * Mp + r] = acc[q];
+            }
         }
-        Yt[e] = acc;
     }
     __syncthreads();
+    // 1 / y_d, y_d = 2 pi (r / M' - d); the limit 1 of P_0 at r = 0
+    const int dk = DK > 0 ? DK : a.dk, terms = 2 * dk + 1;
+    for (int e = threadIdx.x; e < terms * Mp; e += kMergeThreads) {
+        int r;
+        const int d = div_small(e, Mp, inv_mp, &r) - dk;
+        inv_y[e] = r == 0 ? (d == 0 ? 1.f : 0.f)
+                          : __builtin_amdgcn_rcpf(6.28318530717958648f * ((float)r * inv_mp - (float)d));
+    }
+    __syncthreads();
+    const bool whole = k_min == ks_first - dk && k_max == ks_last + dk;  // no term outside the stored band
     if (rows == 0) {
         for (int u = u0 + (int)threadIdx.x; u < u1; u += kMergeThreads) {
             const int q = u - n / 2;
@@ -431,23 +465,29 @@ __global__ __launch_bounds__(kMergeThreads) void rsf_sft_dftmerge_k(SftMergeArgs
         const float sy = __builtin_amdgcn_sinf(fr);        // sin(2 pi r / M')
         const float sh2 = __builtin_amdgcn_sinf(0.5f * fr);  // sin(pi r / M')
         const float omc = 2.0f * sh2 * sh2;                // 1 - cos y
-        const int d_lo = (int)max((int64_t)-a.dk, a.k_lo - ks);
-        const int d_hi = (int)min((int64_t)a.dk, a.k_lo + a.K - 1 - ks);
         const int kr0 = (int)(ks - k_min);                 // row of d = 0
-        float2 acc = make_float2(0.f, 0.f);
+        float2 sum = make_float2(0.f, 0.f);
+        if (whole) {
+            const float2* yr = Yt + (kr0 - dk) * Mp + r;
+            const float* iv = inv_y + r;
 #pragma unroll
-        for (int t = 0; t <= 2 * DK; ++t) {
-            const int d = t - DK;
-            const float2 v = Yt[min(max(kr0 + d, 0), rows - 1) * Mp + r];
-            const float inv = __builtin_amdgcn_rcpf(6.28318530717958648f * (fr - (float)d));
-            float px = r == 0 ? (d == 0 ? 1.f : 0.f) : sy * inv;
-            float py = r == 0 ? 0.f : -omc * inv;
-            const bool on = d >= d_lo && d <= d_hi;
-            px = on ? px : 0.f;
-            py = on ? py : 0.f;
-            acc.x += v.x * px - v.y * py;
-            acc.y += v.x * py + v.y * px;
+            for (int t = 0; t < (DK > 0 ? 2 * DK + 1 : terms); ++t) {
+                const float2 v = yr[t * Mp];
+                const float c = iv[t * Mp];
+                sum.x += c * v.x;
+                sum.y += c * v.y;
+            }
+        } else {
+            const int t_lo = max(0, dk - kr0), t_hi = min(terms, rows + dk - kr0);
+            for (int t = t_lo; t < t_hi; ++t) {
+                const float2 v = Yt[(kr0 - dk + t) * Mp + r];
+                const float c = inv_y[t * Mp + r];
+                sum.x += c * v.x;
+                sum.y += c * v.y;
+            }
         }
+        const float px = r == 0 ? 1.f : sy, py = r == 0 ? 0.f : -omc;
+        const float2 acc = make_float2(sum.x * px - sum.y * py, sum.x * py + sum.y * px);
         float wgt = 1.0f;
         if (a.taper > 0.f) {
             const float x = ((float)u + 0.5f) / (float)n;
@@ -561,6 +601,13 @@ __global__ __launch_bounds__(kNT) void rsf_sft_rows_k(SftRowsArgs A) {
     lds_fft_into<kNT, kFftEPT, RB, false>(lds, st, tws, Interleaved<RB>{}, sink, NoMid{});
 }
 
+// Zeros in the output's gaps (the columns pass writes everything else).
+__global__ __launch_bounds__(256) void rsf_sft_gaps_k(const int64_t* __restrict__ gaps, float2* __restrict__ x) {
+    const int64_t lo = gaps[2 * blockIdx.y], hi = gaps[2 * blockIdx.y + 1];
+    for (int64_t j = lo + (int64_t)blockIdx.x * 256 + threadIdx.x; j < hi; j += (int64_t)gridDim.x * 256)
+        x[j] = make_float2(0.f, 0.f);
+}
+
 // One chunk's output: transform value (re, im) at j = k_a + LA k_b goes to
 // x[j0 + j] for j < n_keep, conjugated, tapered at the edges and phase
 // corrected.
@@ -646,6 +693,14 @@ __global__ __launch_bounds__(kNTB) void rsf_sft_cols_k(SftColsArgs B) {
     lds_fft_into<kNTB, kPassBEPT, CB, false>(lds, st, tw, Grouped8{LB * kGroupCols}, sink, NoMid{});
 }
 
+hipError_t launch_sft_gaps(const int64_t* gaps, int n_gaps, int64_t longest, float2* x, hipStream_t s) {
+    const unsigned gx = (unsigned)std::min<int64_t>((longest + 255) / 256, 256);
+    for (int g0 = 0; g0 < n_gaps; g0 += 65535)
+        hipLaunchKernelGGL(rsf_sft_gaps_k, dim3(gx, (unsigned)std::min(n_gaps - g0, 65535)), dim3(256), 0, s,
+                           gaps + 2 * g0, x);
+    return hipGetLastError();
+}
+
 hipError_t launch_sft_norm(const SftNormArgs& a, int n_sft, hipStream_t s) {
     if (a.w <= kNormRegMax) {
         const unsigned gx = (unsigned)((a.K + kNormTile - 1) / kNormTile);
@@ -678,11 +733,10 @@ size_t sft_fused_lds(int M, int Mp, int dk) {
 }
 
 hipError_t launch_sft_dftmerge(const SftMergeArgs& a, int64_t blocks, size_t lds, hipStream_t s) {
-    static_assert(2 * 16 + 1 == kSftMaxTerms, "the wide merge instance covers every dk");
-    if (a.dk <= 8)
+    if (a.dk == 8)
         hipLaunchKernelGGL(rsf_sft_dftmerge_k<8>, dim3((unsigned)blocks), dim3(kMergeThreads), lds, s, a);
     else
-        hipLaunchKernelGGL(rsf_sft_dftmerge_k<16>, dim3((unsigned)blocks), dim3(kMergeThreads), lds, s, a);
+        hipLaunchKernelGGL(rsf_sft_dftmerge_k<0>, dim3((unsigned)blocks), dim3(kMergeThreads), lds, s, a);
     return hipGetLastError();
 }
 
