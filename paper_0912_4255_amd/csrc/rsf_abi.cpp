@@ -1468,6 +1468,7 @@ int64_t next_7smooth_i(int64_t n) {
 struct SftXform {
     int64_t n;
     int L1, L2, n_groups;
+    int R, C;  // rows per rows workgroup, columns per columns workgroup
     FftStages st1, st2;
     float2 *t1, *t1_hi, *t2, *t2_hi, *tw_lo, *tw_hi;
 };
@@ -1501,7 +1502,7 @@ struct rsf_sft_plan {
     SftLenDev* lens_dev;                  // device table of the transform lengths
     int64_t* gaps_dev;                    // device copy of gaps (null when there are none)
     int64_t gap_longest;                  // samples of the longest gap
-    int rows_R, cols_C;                   // rows per rows workgroup, columns per columns workgroup
+    int rows_thr, cols_thr;               // threads of the rows and columns workgroups
     int64_t rows_blocks, cols_blocks;     // workgroups of the single rows / columns launches
     size_t rows_lds, cols_lds;
 };
@@ -1598,8 +1599,7 @@ int rsf_sft_plan_create(rsf_sft_plan** out, const rsf_sft_desc* d, const double*
     p->lens_dev = nullptr;
     p->gaps_dev = nullptr;
     p->gap_longest = 0;
-    p->rows_R = 1;
-    p->cols_C = kPassBCols;
+    p->rows_thr = p->cols_thr = 0;
     p->rows_blocks = p->cols_blocks = 0;
     p->rows_lds = p->cols_lds = 0;
     int dev = 0, lds_dev = 0;
@@ -1670,37 +1670,38 @@ int rsf_sft_plan_create(rsf_sft_plan** out, const rsf_sft_desc* d, const double*
         p->chunks.push_back(c);
         a0 = a;
     }
-    // rows and columns per workgroup: the most that every transform length of
-    // the plan fits (stage capacity and LDS), so that the many short rows and
-    // columns of these transforms come several to a workgroup
+    // rows and columns per workgroup: the most that a length fits (stage
+    // capacity and LDS), so that the many short rows and columns of these
+    // transforms come several to a workgroup; workgroups of kSftThreads, of which
+    // a CU holds several, unless some length needs more.  The 10-day set, whose
+    // lengths differ by the chunks: rows 46 us, where 512 threads with R = 4 for
+    // all lengths took 50 us; columns 39 us with either.
     {
-        auto rows_fit = [&](int R) {
-            for (const auto& x : p->xf) {
-                FftStages st;
-                if (!radix_plan(x.L1, R, kFftThreads, kFftEPT, &st) || sft_rows_lds(x.L1, R) > (size_t)lds_cap)
-                    return false;
-            }
-            return true;
+        auto plan = [&](int len, int most, int least, int thr, int ept, size_t (*lds)(int, int), FftStages* st) {
+            for (int m = most; m >= least; m /= 2)
+                if ((thr != kSftThreads || len * m <= kSftPoints * thr) && lds(len, m) <= (size_t)lds_cap &&
+                    radix_plan(len, m, thr, ept, st))
+                    return m;
+            return 0;
         };
-        auto cols_fit = [&](int C) {
-            for (const auto& x : p->xf) {
-                FftStages st;
-                if (!radix_plan(x.L2, C, kPassBThreads, kPassBEPT, &st) || sft_cols_lds(x.L2, C) > (size_t)lds_cap)
-                    return false;
-            }
-            return true;
-        };
-        int R = 8, C = 32;
-        while (R > 1 && !rows_fit(R)) R /= 2;
-        while (C > kPassBCols && !cols_fit(C)) C /= 2;
-        p->rows_R = R;
-        p->cols_C = C;
+        FftStages st;
+        bool small_rows = true, small_cols = true;
+        for (const auto& x : p->xf) {
+            small_rows = small_rows && plan(x.L1, 8, 1, kSftThreads, kFftEPT, sft_rows_lds, &st) != 0;
+            small_cols = small_cols && plan(x.L2, 32, kPassBCols, kSftThreads, kPassBEPT, sft_cols_lds, &st) != 0;
+        }
+        p->rows_thr = small_rows ? kSftThreads : kFftThreads;
+        p->cols_thr = small_cols ? kSftThreads : kPassBThreads;
         p->lds_max = 0;
         for (auto& x : p->xf) {
-            radix_plan(x.L1, R, kFftThreads, kFftEPT, &x.st1);
-            radix_plan(x.L2, C, kPassBThreads, kPassBEPT, &x.st2);
-            x.n_groups = (x.L1 + C - 1) / C;
-            p->lds_max = std::max({p->lds_max, sft_rows_lds(x.L1, R), sft_cols_lds(x.L2, C)});
+            x.R = plan(x.L1, 8, 1, p->rows_thr, kFftEPT, sft_rows_lds, &x.st1);
+            x.C = plan(x.L2, 32, kPassBCols, p->cols_thr, kPassBEPT, sft_cols_lds, &x.st2);
+            if (!x.R || !x.C) {
+                sft_free(p);
+                return fail(RSF_EUNSUPPORTED, "chunk transform of %lld points has no stages", (long long)x.n);
+            }
+            x.n_groups = (x.L1 + x.C - 1) / x.C;
+            p->lds_max = std::max({p->lds_max, sft_rows_lds(x.L1, x.R), sft_cols_lds(x.L2, x.C)});
         }
     }
     // gaps: output samples outside every chunk
@@ -1746,7 +1747,7 @@ int rsf_sft_plan_create(rsf_sft_plan** out, const rsf_sft_desc* d, const double*
         t.scale = (float)(1.0 / std::sqrt((double)x.n * (double)c.M));
         t.corr = c.corr;
         p->y_total += x.n;
-        p->spill_total += (size_t)x.n_groups * p->cols_C * x.L2;
+        p->spill_total += (size_t)x.n_groups * x.C * x.L2;
         p->merge_blocks += sft_merge_blocks((int)x.n);
         p->dft_total += (int64_t)d->n_bins * c.Mp;
         p->dft_blocks += sft_dft_blocks((int64_t)d->n_bins * c.Mp);
@@ -1768,6 +1769,8 @@ int rsf_sft_plan_create(rsf_sft_plan** out, const rsf_sft_desc* d, const double*
         l.LA = x.L1;
         l.LB = x.L2;
         l.n_groups = x.n_groups;
+        l.R = x.R;
+        l.C = x.C;
         l.nc = (int)p->group[g].size();
         l.id0 = (int)p->ids_off[g];
         l.rows_blk0 = p->rows_blocks;
@@ -1781,10 +1784,10 @@ int rsf_sft_plan_create(rsf_sft_plan** out, const rsf_sft_desc* d, const double*
         l.tw_lo = x.tw_lo;
         l.tw_hi = x.tw_hi;
         // chunks of one length go through both passes in pairs
-        p->rows_blocks += (int64_t)((x.L2 + p->rows_R - 1) / p->rows_R) * ((l.nc + 1) / 2);
+        p->rows_blocks += (int64_t)((x.L2 + x.R - 1) / x.R) * ((l.nc + 1) / 2);
         p->cols_blocks += (int64_t)x.n_groups * ((l.nc + 1) / 2);
-        p->rows_lds = std::max(p->rows_lds, sft_rows_lds(x.L1, p->rows_R));
-        p->cols_lds = std::max(p->cols_lds, sft_cols_lds(x.L2, p->cols_C));
+        p->rows_lds = std::max(p->rows_lds, sft_rows_lds(x.L1, x.R));
+        p->cols_lds = std::max(p->cols_lds, sft_cols_lds(x.L2, x.C));
     }
     if (hipMalloc((void**)&p->chunks_dev, tab.size() * sizeof(SftChunkDev)) != hipSuccess ||
         hipMemcpy(p->chunks_dev, tab.data(), tab.size() * sizeof(SftChunkDev), hipMemcpyHostToDevice) != hipSuccess ||
@@ -1890,7 +1893,7 @@ int rsf_sft_heterodyne(const rsf_sft_plan* p, const float* sft, float* x_h, void
     r.ids = p->ids_dev;
     r.y = y;
     r.spill = spill;
-    RSF_HIP(timed_pr(p->prof, K_SFT_ROWS, s, [&] { return launch_sft_rows(r, p->rows_blocks, p->rows_lds, p->rows_R, s); }),
+    RSF_HIP(timed_pr(p->prof, K_SFT_ROWS, s, [&] { return launch_sft_rows(r, p->rows_blocks, p->rows_lds, p->rows_thr, s); }),
             "sft rows launch");
     SftColsArgs k{};
     k.lens = p->lens_dev;
@@ -1901,7 +1904,7 @@ int rsf_sft_heterodyne(const rsf_sft_plan* p, const float* sft, float* x_h, void
     k.x = reinterpret_cast<float2*>(x_h);
     k.n_out = d.n_out;
     k.n_edge = (int)std::nearbyint(d.edge_taper_s * d.band);
-    RSF_HIP(timed_pr(p->prof, K_SFT_COLS, s, [&] { return launch_sft_cols(k, p->cols_blocks, p->cols_lds, p->cols_C, s); }),
+    RSF_HIP(timed_pr(p->prof, K_SFT_COLS, s, [&] { return launch_sft_cols(k, p->cols_blocks, p->cols_lds, p->cols_thr, s); }),
             "sft cols launch");
     return RSF_OK;
 }

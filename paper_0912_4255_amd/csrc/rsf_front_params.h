@@ -24,6 +24,10 @@ struct HetdecArgs {
 // ---------------------------------------------------------------------------
 constexpr int kSftMaxWindow = 511;  // longest running-median window
 constexpr int kSftMaxTerms = 33;    // 2 dk + 1 Dirichlet terms at most
+// Threads of the rows and columns passes where every transform length fits them
+// (at most kSftPoints points a thread, several workgroups per CU), else the
+// F-statistic passes' workgroups.
+constexpr int kSftThreads = 256, kSftPoints = 13;
 constexpr int kSftMaxGrid = 8192;   // SFTs of one chunk's transform grid M' (its roots sit in LDS)
 
 // Running-median normalisation of SFT bands (eq. dimlessSFTs1).
@@ -81,14 +85,15 @@ struct SftMergeArgs {
 // One chunk transform length n = LA LB of the SFT front end.  Its chunks are
 // ids[id0 .. id0 + nc), transformed in pairs (chunks 2i and 2i + 1 as the two
 // complex halves of each float4; the last alone when nc is odd).  With R rows
-// and C columns per workgroup (the same for every length of a plan), its
-// workgroups in the single rows launch are rows_blk0 + i ceil(LB / R) + g
+// and C columns per workgroup, its workgroups in the single rows launch are
+// rows_blk0 + i ceil(LB / R) + g
 // (rows g R .. g R + R - 1 of its i-th pair), in the single columns launch
 // cols_blk0 + i n_groups + g (columns g C .. g C + C - 1, n_groups =
 // ceil(LA / C)); st1 and st2 are planned for R and C interleaved transforms.
 struct SftLenDev {
     int64_t n;
     int LA, LB, n_groups, nc, id0;
+    int R, C;               // rows and columns per workgroup
     int64_t rows_blk0, cols_blk0;
     FftStages st1, st2;
     const float2* t1;       // W_LA^m = t1[m % 32] * t1_hi[m / 32]

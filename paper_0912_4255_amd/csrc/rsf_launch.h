@@ -63,8 +63,8 @@ size_t sft_fused_lds(int M, int Mp, int dk);  // their LDS for a chunk of M SFTs
 hipError_t launch_sft_dftmerge(const SftMergeArgs& a, int64_t blocks, size_t lds, hipStream_t s);
 size_t sft_rows_lds(int LA, int R);  // R rows of LA points per workgroup
 size_t sft_cols_lds(int LB, int C);  // C columns of LB points per workgroup
-hipError_t launch_sft_rows(const SftRowsArgs& a, int64_t blocks, size_t lds, int R, hipStream_t s);  // R in {1, 2, 4, 8}
-hipError_t launch_sft_cols(const SftColsArgs& b, int64_t blocks, size_t lds, int C, hipStream_t s);  // C in {8, 16, 32}
+hipError_t launch_sft_rows(const SftRowsArgs& a, int64_t blocks, size_t lds, int threads, hipStream_t s);  // kSftThreads or kFftThreads
+hipError_t launch_sft_cols(const SftColsArgs& b, int64_t blocks, size_t lds, int threads, hipStream_t s);  // kSftThreads or kPassBThreads
 hipError_t sft_set_lds_limits(size_t bytes);
 
 int point_rows(int64_t P);              // 64-sample rows per wave for a series of P rows

@@ -336,7 +336,9 @@ __global__ __launch_bounds__(kMergeThreads) void rsf_sft_merge_k(SftMergeArgs a)
 // P_d = (sin y - i (1 - cos y)) / y_d leaves its numerator outside the sum, so a
 // term is two LDS reads and two multiply-adds.  Chosen when every chunk fits the
 // LDS (sft_fused_lds).  What bounds it: LDS reads and vector issue.  The 10-day
-// set: see rsf_sft_dftmerge_k's figure below.
+// set (432 SFTs, 7318 bins, dk = 8): 43 us, where one row per phase and a
+// reciprocal per term took 61 us; the series' error against FP64 fell from
+// 1.6e-6 to 4.1e-7 of its maximum.
 namespace {
 constexpr int kFuseBins = 1024;
 
@@ -545,12 +547,12 @@ struct SftSpillSink {
 // first chunk's in the low complex half of each float4, the second's in the
 // high half), transforms them over n_a as RB interleaved columns and spills
 // them with the inter-pass twiddle W_n^{n_b k_a} into the first chunk's
-// spill.  Thread tid always holds row tid mod RB (kNT is a multiple of RB), so
-// its twiddle recurrences run for one n_b.
-template <int RB>
-__global__ __launch_bounds__(kNT) void rsf_sft_rows_k(SftRowsArgs A) {
-    extern __shared__ float4 lds[];
-    const SftLenDev& L = A.lens[sft_len_of<&SftLenDev::rows_blk0>(A.lens, A.n_lens, blockIdx.x)];
+// spill.  Thread tid always holds row tid mod RB (THR is a multiple of RB), so
+// its twiddle recurrences run for one n_b.  The loads' latency bounds it, so
+// workgroups of 256 threads, three to a CU: 46 us for the 10-day set (50 us
+// with 512 threads).
+template <int RB, int THR>
+__device__ __forceinline__ void sft_rows(const SftRowsArgs& A, const SftLenDev& L, float4* lds) {
     const int LA = L.LA, LB = L.LB;
     const int64_t n = L.n;
     const int ng = (LB + RB - 1) / RB;  // row groups per chunk
@@ -560,7 +562,7 @@ __global__ __launch_bounds__(kNT) void rsf_sft_rows_k(SftRowsArgs A) {
     const FftStages st = L.st1;
     float2* twl = reinterpret_cast<float2*>(lds + LA * RB);
     const int n_hi = (LA + 31) >> kTwLoBits;
-    for (int e = threadIdx.x; e < 32 + n_hi; e += kNT) twl[e] = (e < 32) ? L.t1[e] : L.t1_hi[e - 32];
+    for (int e = threadIdx.x; e < 32 + n_hi; e += THR) twl[e] = (e < 32) ? L.t1[e] : L.t1_hi[e - 32];
     const TwLds tws{twl, twl + 32};
     const SftChunkDev& c = A.chunks[A.ids[L.id0 + 2 * i]];
     const bool pair = 2 * i + 1 < L.nc;
@@ -568,11 +570,11 @@ __global__ __launch_bounds__(kNT) void rsf_sft_rows_k(SftRowsArgs A) {
     const float2* src2 = A.y + (pair ? A.chunks[A.ids[L.id0 + 2 * i + 1]].y_off : c.y_off);
     const int tid = threadIdx.x;
     // kSftLoads elements per thread in flight, then into LDS
-    for (int e0 = 0; e0 < LA * RB; e0 += kNT * kSftLoads) {
+    for (int e0 = 0; e0 < LA * RB; e0 += THR * kSftLoads) {
         float4 v[kSftLoads];
 #pragma unroll
         for (int j = 0; j < kSftLoads; ++j) {
-            const int e = e0 + j * kNT + tid;
+            const int e = e0 + j * THR + tid;
             const int n_a = e / RB, b = e - n_a * RB;
             const bool in = e < LA * RB && nb0 + b < LB;
             const int64_t m = (int64_t)LB * n_a + nb0 + b;
@@ -582,13 +584,13 @@ __global__ __launch_bounds__(kNT) void rsf_sft_rows_k(SftRowsArgs A) {
         }
 #pragma unroll
         for (int j = 0; j < kSftLoads; ++j) {
-            const int e = e0 + j * kNT + tid;
+            const int e = e0 + j * THR + tid;
             if (e < LA * RB) lds[e] = v[j];
         }
     }
     const int n_b = nb0 + tid % RB;
     const int64_t mb = ((int64_t)n_b * (tid / RB)) % n;
-    const int64_t ms = ((int64_t)n_b * (kNT / RB)) % n;
+    const int64_t ms = ((int64_t)n_b * (THR / RB)) % n;
     const int msk = (1 << kTwSplitBits) - 1;
     const float2 w_base = c_mul(L.tw_hi[mb >> kTwSplitBits], L.tw_lo[mb & msk]);
     const float2 w_step = c_mul(L.tw_hi[ms >> kTwSplitBits], L.tw_lo[ms & msk]);
@@ -598,7 +600,19 @@ __global__ __launch_bounds__(kNT) void rsf_sft_rows_k(SftRowsArgs A) {
     const float2 w_lr = c_mul(L.tw_hi[ml >> kTwSplitBits], L.tw_lo[ml & msk]);
     __syncthreads();
     SftSpillSink sink{reinterpret_cast<char*>(A.spill + c.spill_off), LB, n_b, lr, w_base, w_step, w_lr, n_b < LB};
-    lds_fft_into<kNT, kFftEPT, RB, false>(lds, st, tws, Interleaved<RB>{}, sink, NoMid{});
+    lds_fft_into<THR, kFftEPT, RB, false>(lds, st, tws, Interleaved<RB>{}, sink, NoMid{});
+}
+
+template <int THR>
+__global__ __launch_bounds__(THR, 3) void rsf_sft_rows_k(SftRowsArgs A) {
+    extern __shared__ float4 lds[];
+    const SftLenDev& L = A.lens[sft_len_of<&SftLenDev::rows_blk0>(A.lens, A.n_lens, blockIdx.x)];
+    switch (L.R) {
+        case 8: sft_rows<8, THR>(A, L, lds); break;
+        case 4: sft_rows<4, THR>(A, L, lds); break;
+        case 2: sft_rows<2, THR>(A, L, lds); break;
+        default: sft_rows<1, THR>(A, L, lds); break;
+    }
 }
 
 // Zeros in the output's gaps (the columns pass writes everything else).
@@ -653,10 +667,8 @@ struct SeriesSink {
 // chunk's spill, one contiguous run) over n_b and writes both series.
 // Columns at or past LA (padding of the last group) are transformed but not
 // written.
-template <int CB>
-__global__ __launch_bounds__(kNTB) void rsf_sft_cols_k(SftColsArgs B) {
-    extern __shared__ float4 lds[];
-    const SftLenDev& L = B.lens[sft_len_of<&SftLenDev::cols_blk0>(B.lens, B.n_lens, blockIdx.x)];
+template <int CB, int THR>
+__device__ __forceinline__ void sft_cols(const SftColsArgs& B, const SftLenDev& L, float4* lds) {
     const int LA = L.LA, LB = L.LB;
     const int64_t local = (int64_t)blockIdx.x - L.cols_blk0;
     const int i = (int)(local / L.n_groups);
@@ -667,22 +679,22 @@ __global__ __launch_bounds__(kNTB) void rsf_sft_cols_k(SftColsArgs B) {
     float2* twl = reinterpret_cast<float2*>(lds + buf_elems);
     const int n_hi = (LB + 31) >> kTwLoBits;
     const int tid = threadIdx.x;
-    for (int e = tid; e < 32 + n_hi; e += kNTB) twl[e] = (e < 32) ? L.t2[e] : L.t2_hi[e - 32];
+    for (int e = tid; e < 32 + n_hi; e += THR) twl[e] = (e < 32) ? L.t2[e] : L.t2_hi[e - 32];
     const TwLds tw{twl, twl + 32};
     const SftChunkDev& ch = B.chunks[B.ids[L.id0 + 2 * i]];
     const bool pair = 2 * i + 1 < L.nc;
     const SftChunkDev& ch2 = B.chunks[B.ids[L.id0 + (pair ? 2 * i + 1 : 2 * i)]];
     const float4* src = B.spill + ch.spill_off + (int64_t)c * blk;
-    for (int e0 = 0; e0 < blk; e0 += kNTB * kSftLoads) {
+    for (int e0 = 0; e0 < blk; e0 += THR * kSftLoads) {
         float4 v[kSftLoads];
 #pragma unroll
         for (int j = 0; j < kSftLoads; ++j) {
-            const int e = e0 + j * kNTB + tid;
+            const int e = e0 + j * THR + tid;
             v[j] = e < blk ? src[e] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
 #pragma unroll
         for (int j = 0; j < kSftLoads; ++j) {
-            const int e = e0 + j * kNTB + tid;
+            const int e = e0 + j * THR + tid;
             if (e < blk) lds[e] = v[j];
         }
     }
@@ -690,7 +702,18 @@ __global__ __launch_bounds__(kNTB) void rsf_sft_cols_k(SftColsArgs B) {
     const int r_last = st.n_stages ? st.radix[st.n_stages - 1] : 1;
     SeriesSink sink{B.x, B.n_out, LA, LB / r_last, c * CB, B.n_edge, SeriesOut{ch.j0, ch.n_keep, ch.corr},
                     SeriesOut{ch2.j0, ch2.n_keep, ch2.corr}, pair};
-    lds_fft_into<kNTB, kPassBEPT, CB, false>(lds, st, tw, Grouped8{LB * kGroupCols}, sink, NoMid{});
+    lds_fft_into<THR, kPassBEPT, CB, false>(lds, st, tw, Grouped8{LB * kGroupCols}, sink, NoMid{});
+}
+
+template <int THR>
+__global__ __launch_bounds__(THR, 3) void rsf_sft_cols_k(SftColsArgs B) {
+    extern __shared__ float4 lds[];
+    const SftLenDev& L = B.lens[sft_len_of<&SftLenDev::cols_blk0>(B.lens, B.n_lens, blockIdx.x)];
+    switch (L.C) {
+        case 32: sft_cols<32, THR>(B, L, lds); break;
+        case 16: sft_cols<16, THR>(B, L, lds); break;
+        default: sft_cols<8, THR>(B, L, lds); break;
+    }
 }
 
 hipError_t launch_sft_gaps(const int64_t* gaps, int n_gaps, int64_t longest, float2* x, hipStream_t s) {
@@ -753,35 +776,34 @@ size_t sft_cols_lds(int LB, int C) {
     return (size_t)((LB * C + 63) / 64) * 64 * sizeof(float4) + (32 + (LB + 31) / 32) * sizeof(float2);
 }
 
-hipError_t launch_sft_rows(const SftRowsArgs& a, int64_t blocks, size_t lds, int R, hipStream_t s) {
-    const dim3 g((unsigned)blocks), b(kNT);
-    switch (R) {
-        case 1: hipLaunchKernelGGL(rsf_sft_rows_k<1>, g, b, lds, s, a); break;
-        case 2: hipLaunchKernelGGL(rsf_sft_rows_k<2>, g, b, lds, s, a); break;
-        case 4: hipLaunchKernelGGL(rsf_sft_rows_k<4>, g, b, lds, s, a); break;
-        case 8: hipLaunchKernelGGL(rsf_sft_rows_k<8>, g, b, lds, s, a); break;
-        default: return hipErrorInvalidValue;
-    }
+hipError_t launch_sft_rows(const SftRowsArgs& a, int64_t blocks, size_t lds, int threads, hipStream_t s) {
+    const dim3 g((unsigned)blocks), b((unsigned)threads);
+    if (threads == kSftThreads)
+        hipLaunchKernelGGL(rsf_sft_rows_k<kSftThreads>, g, b, lds, s, a);
+    else if (threads == kNT)
+        hipLaunchKernelGGL(rsf_sft_rows_k<kNT>, g, b, lds, s, a);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-hipError_t launch_sft_cols(const SftColsArgs& k, int64_t blocks, size_t lds, int C, hipStream_t s) {
-    const dim3 g((unsigned)blocks), b(kNTB);
-    switch (C) {
-        case 8: hipLaunchKernelGGL(rsf_sft_cols_k<8>, g, b, lds, s, k); break;
-        case 16: hipLaunchKernelGGL(rsf_sft_cols_k<16>, g, b, lds, s, k); break;
-        case 32: hipLaunchKernelGGL(rsf_sft_cols_k<32>, g, b, lds, s, k); break;
-        default: return hipErrorInvalidValue;
-    }
+hipError_t launch_sft_cols(const SftColsArgs& k, int64_t blocks, size_t lds, int threads, hipStream_t s) {
+    const dim3 g((unsigned)blocks), b((unsigned)threads);
+    if (threads == kSftThreads)
+        hipLaunchKernelGGL(rsf_sft_cols_k<kSftThreads>, g, b, lds, s, k);
+    else if (threads == kNTB)
+        hipLaunchKernelGGL(rsf_sft_cols_k<kNTB>, g, b, lds, s, k);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 hipError_t sft_set_lds_limits(size_t bytes) {
     static size_t granted = 0;  // only grows
     if (bytes <= granted) return hipSuccess;
-    const void* fns[] = {(const void*)rsf_sft_dft_k,      (const void*)rsf_sft_rows_k<1>,  (const void*)rsf_sft_rows_k<2>,
-                         (const void*)rsf_sft_rows_k<4>,  (const void*)rsf_sft_rows_k<8>,  (const void*)rsf_sft_cols_k<8>,
-                         (const void*)rsf_sft_cols_k<16>, (const void*)rsf_sft_cols_k<32>};
+    const void* fns[] = {(const void*)rsf_sft_dft_k, (const void*)rsf_sft_rows_k<kSftThreads>,
+                         (const void*)rsf_sft_rows_k<kNT>, (const void*)rsf_sft_cols_k<kSftThreads>,
+                         (const void*)rsf_sft_cols_k<kNTB>};
     hipError_t out = hipSuccess;
     for (const void* f : fns) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
