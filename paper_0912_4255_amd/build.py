@@ -20,8 +20,8 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "librsfstat.so")
 
-SOURCES = ["rsf_abi.cpp", "rsf_rtc.cpp", "rsf_resample.hip", "rsf_fft.hip", "rsf_point.hip", "rsf_topk.hip", "rsf_sft.hip",
-           "rsf_semico.hip", "rsf_hetdec.hip"]
+SOURCES = ["rsf_abi.cpp", "rsf_rtc.cpp", "rsf_resample.hip", "rsf_fft.hip", "rsf_fft_rows.hip", "rsf_point.hip", "rsf_topk.hip",
+           "rsf_sft.hip", "rsf_semico.hip", "rsf_hetdec.hip"]
 # the headers a first-pass row plan compiled at run time is built from (their
 # hash is recorded in the library, which compiles only from matching ones)
 ROW_HEADERS = ["rsf_pass_a.h", "rsf_device.h", "rsf_spill.h", "rsf_params.h"]

@@ -640,13 +640,13 @@ const FixedRow kFixedRows[] = {
 #undef RSF_ROW_FN
 constexpr int kNumFixedRows = (int)(sizeof(kFixedRows) / sizeof(kFixedRows[0]));
 
-// The general-stage kernels [threads and stage capacity][spindown order - 1][non-temporal spill].
+// The general-stage kernels of 512 threads [stage capacity][spindown order - 1]
+// [non-temporal spill]; kGeneralRowsSmall has those of 128 and 256.
 #define RSF_GENERAL_FN(ORD, EPT, THR)                                        \
     {(const void*)rsf_fft_pass_a_k<ORD, false, GeneralStages<EPT>, THR>,     \
      (const void*)rsf_fft_pass_a_k<ORD, true, GeneralStages<EPT>, THR>}
 #define RSF_GENERAL(EPT, THR) {RSF_GENERAL_FN(1, EPT, THR), RSF_GENERAL_FN(2, EPT, THR), RSF_GENERAL_FN(3, EPT, THR)}
-const void* const kGeneralRows[4][3][2] = {RSF_GENERAL(kFftEPT, 128), RSF_GENERAL(kFftEPT, 256),
-                                           RSF_GENERAL(kFftEPT, kFftThreads), RSF_GENERAL(kFftEPTWide, kFftThreads)};
+const void* const kGeneralRows[2][3][2] = {RSF_GENERAL(kFftEPT, kFftThreads), RSF_GENERAL(kFftEPTWide, kFftThreads)};
 #undef RSF_GENERAL
 #undef RSF_GENERAL_FN
 
@@ -716,8 +716,10 @@ hipError_t launch_fft_pass_a(const PassAArgs& a, hipStream_t s, void* const* row
     if (fi < 0) thr = (unsigned)general_row_threads(a.st, a.ept, a.LB);
     if (fi >= 0)
         fn = kFixedRows[fi].fn[a.spin_order - 1][nt];
-    else if (a.ept == kFftEPT || (a.ept == kFftEPTWide && thr == kFftThreads))
-        fn = kGeneralRows[a.ept == kFftEPTWide ? 3 : thr == 128 ? 0 : thr == 256 ? 1 : 2][a.spin_order - 1][nt];
+    else if (a.ept == kFftEPT && thr < (unsigned)kFftThreads)
+        fn = kGeneralRowsSmall[thr == 128 ? 0 : 1][a.spin_order - 1][nt];
+    else if (a.ept == kFftEPT || a.ept == kFftEPTWide)
+        fn = kGeneralRows[a.ept == kFftEPTWide ? 1 : 0][a.spin_order - 1][nt];
     else
         return hipErrorInvalidValue;
     return hipLaunchKernel(fn, grid, dim3(thr), args, lds, s);
@@ -807,6 +809,9 @@ hipError_t fft_set_lds_limits(size_t bytes) {
     };
     for (const void* f : fns) set(f);
     for (const auto& c : kGeneralRows)
+        for (const auto& o : c)
+            for (const void* f : o) set(f);
+    for (const auto& c : kGeneralRowsSmall)
         for (const auto& o : c)
             for (const void* f : o) set(f);
     for (const FixedRow& r : kFixedRows)

@@ -15,6 +15,10 @@ int resample_blocks(int LB, int64_t P);
 bool resample_interpolates(double dt, const EphDev& e);  // the interpolated timing chain holds at this sampling interval
 hipError_t launch_antenna_reduce(const ReduceArgs& r, hipStream_t s);
 
+// The first pass's general-stage kernels of 128 and 256 threads
+// [threads][spindown order - 1][non-temporal spill].
+extern const void* const kGeneralRowsSmall[2][3][2];
+
 // row_fn: a run-time compiled RowPlan kernel of a.st per non-temporal flag
 // (row_plan_kernels), used when no compiled-in plan serves the launch.
 hipError_t launch_fft_pass_a(const PassAArgs& a, hipStream_t s, void* const* row_fn = nullptr);
