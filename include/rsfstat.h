@@ -492,7 +492,9 @@ typedef struct rsf_hetdec_plan rsf_hetdec_plan;
 int rsf_hetdec_plan_create(rsf_hetdec_plan** out, const rsf_hetdec_desc* desc);
 int rsf_hetdec_plan_destroy(rsf_hetdec_plan* plan);
 /* x: float32 [n_raw] (device); x_h: complex64 [n_out] (device, overwritten).
- * No workspace.  Asynchronous on `stream`. */
+ * No workspace.  Asynchronous on `stream`.  An output's bits depend on the filter
+ * and on the samples near it, not on n_raw, n_out or the device.  A raw sample
+ * that is not finite affects only the outputs whose filter reaches it. */
 int rsf_hetdec(const rsf_hetdec_plan* plan, const float* x, float* x_h, void* stream);
 int rsf_hetdec_profile_enable(rsf_hetdec_plan* plan, int on);
 int rsf_hetdec_profile_read(rsf_hetdec_plan* plan, rsf_kernel_time* out, int max_kinds, int* n_kinds);

@@ -5,8 +5,9 @@
 // so the filter runs with complex taps g[i] = h[i] exp(-2 pi i f_h (c - i) dt)
 // on the real series and each output takes one FP64 phase factor.
 //
-// Two forms: filters of at least 4 D + 1 taps whose window fits LDS run as a
-// product on the FP32 matrix cores (rsf_hetdec_mfma_k, below); the others a
+// Two forms: filters of L >= 4 D + 1 taps with L + 7 D <= 5120 whose window
+// fits LDS run as a product on the FP32 matrix cores (rsf_hetdec_mfma_k, below;
+// mm_shape has the rule); the others a
 // direct sum (rsf_hetdec_k): one workgroup per 64 outputs, the raw samples its outputs
 // touch and the taps in LDS, each wave computing four outputs at a time with
 // its lanes striding over the taps (consecutive lanes read consecutive
@@ -91,7 +92,13 @@ __global__ __launch_bounds__(kHdThreads) void rsf_hetdec_k(HetdecArgs a) {
 // columns' zero taps cost 7 / (2 K) more products than the direct sum.  The
 // length Kd is split over WK waves, each holding its slice of G in registers
 // for the whole launch; the 16 / WK row tiles of a block are the other way the
-// waves divide.  Partial tiles are added through LDS (a split sum of WK parts).
+// waves divide.  Whatever WK, an output is the same sum of 16 partial sums in the
+// same order: a wave keeps 16 / WK of them apart and adds them as the sum of the
+// waves' partial tiles through LDS goes on, so the bits depend on the filter alone
+// and the error against 64 bits is the direct sum's (0.94 to 1.05 times it for D =
+// 10 to 128 and K = 8 to 20; one partial sum per wave gave up to 1.23 times it at
+// WK = 4 and 8).  Keeping them apart costs up to 4 % (D = 32, K = 8, 3,000,000
+// outputs: 149 -> 155 us).
 //
 // Persistent workgroups walk consecutive blocks (the overlap of neighbouring
 // windows stays in their caches).  One barrier per block: after it, the next
@@ -133,8 +140,13 @@ struct MmShape {
     int WK = 0, NG = 0, NB = 0;  // NB window buffers
 };
 
-// NG is compiled for these values, 18 and 20 for one buffer only
-constexpr int kMmGroups[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 18, 20};
+// NG is compiled for these values: up to 8 for 4 waves along the taps, 12 for 8 waves and
+// 16 for 16, beyond which the taps do not fit the registers beside the partial
+// sums (D = 50, K = 16, 400,000 outputs: 59.7 us with 16 groups on 8 waves, 49.7
+// with 8 on 16; D = 25, K = 16: 45.8 with 16 groups on 4 waves, 34.4 with 8 on 8);
+// 18 and 20 with one buffer only, so filters of Kd <= 5120
+constexpr int kMmGroups[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 18, 20};
+constexpr int mm_groups_max(int WK, int NB) { return NB == 1 ? 20 : WK == 4 ? 8 : WK == 8 ? 12 : 16; }
 
 int mm_pad(int D) { return (D & 1) ? 0 : 4; }
 
@@ -142,23 +154,21 @@ MmShape mm_shape_of(int L, int D, int WK) {
     MmShape m;
     const int Kd = L + 7 * D, WM = kMmWaves / WK;
     const int need = (Kd + 16 * WK - 1) / (16 * WK);
-    int NG = 0;
-    for (int g : kMmGroups)
-        if (g >= need) {
-            NG = g;
-            break;
-        }
-    if (!NG) return m;
-    // the last row reads KR taps from its start; its window has Kd of them in whole chunks of 8 D
-    const int KR = 16 * NG * WK;
-    const int64_t stride = 8 * D + mm_pad(D), rows = 16 * WM - 1;
-    const int64_t floats = std::max((rows + (Kd + 8 * D - 1) / (8 * D)) * stride,
-                                    rows * stride + KR + (int64_t)(KR / (8 * D)) * mm_pad(D) + 16);
-    const int NB = floats <= mm_buf(2) ? 2 : floats <= mm_buf(1) ? 1 : 0;
-    if (!NB || (NB == 1 ? WK != kMmWaves || NG < 8 : NG > 16)) return m;
-    m.NB = NB;
-    m.WK = WK;
-    m.NG = NG;
+    for (int NG : kMmGroups) {
+        if (NG < need) continue;
+        // the last row reads KR taps from its start; its window has Kd of them in whole chunks of 8 D
+        const int KR = 16 * NG * WK;
+        const int64_t stride = 8 * D + mm_pad(D), rows = 16 * WM - 1;
+        const int64_t floats = std::max((rows + (Kd + 8 * D - 1) / (8 * D)) * stride,
+                                        rows * stride + KR + (int64_t)(KR / (8 * D)) * mm_pad(D) + 16);
+        const int NB = floats <= mm_buf(2) ? 2 : floats <= mm_buf(1) ? 1 : 0;
+        if (NB == 1 && NG == 7) continue;  // the one-buffer kernels start at 8
+        if (!NB || NG > mm_groups_max(WK, NB) || (NB == 1 && (WK != kMmWaves || NG < 8))) return m;
+        m.NB = NB;
+        m.WK = WK;
+        m.NG = NG;
+        return m;
+    }
     return m;
 }
 
@@ -171,7 +181,9 @@ MmShape mm_shape(int L, int D, int64_t n_out, int n_cu) {
         const MmShape m = mm_shape_of(L, D, WK);
         if (!m.WK || (best.WK && m.NB < 2)) continue;
         if (best.WK) {
-            // fewer row tiles per block only where larger blocks leave compute units idle
+            // fewer row tiles per block only where larger blocks leave compute units
+            // idle; the same bits (D = 10, K = 8: 40,000 outputs 7.9 us on 16 waves
+            // and 9.6 on 4, 4,000,000 outputs 171 and 131 us)
             const int64_t per_block = 128 * (kMmWaves / best.WK);
             if ((n_out + per_block - 1) / per_block >= 2 * (int64_t)n_cu) break;
         }
@@ -267,12 +279,11 @@ __global__ __launch_bounds__(kMmThreads) void rsf_hetdec_mfma_k(HetdecArgs a, in
     const int kw = wave % WK, mt = wave / WK;
     const int D = a.D, L = a.L, chunk = 8 * D, stride = chunk + pad;
     const int J = lane & 15, q = lane >> 4;
-    // This wave's group g of 16 taps is kk = 16 (kw + WK g): the waves take
-    // groups in turn, so no partial sum holds the filter's main lobe alone, and
-    // the four taps of a lane have an accumulator each: chains as short as the
-    // direct sum's.  The error against 64 bits is the direct sum's (1.5e-7
-    // relative at D = 100, K = 16); with contiguous slices and two accumulators
-    // it was 2.2e-7 at 158 us.
+    // This wave's group g of 16 taps is kk = 16 (kw + WK g): the partial sums take
+    // groups in turn, so none holds the filter's main lobe alone, and the four taps
+    // of a lane have an accumulator each: chains as short as the direct sum's.
+    // With contiguous slices and two accumulators the error at D = 100, K = 16 was
+    // 2.2e-7 at 158 us, against 1.5e-7.
     // B operand: lane holds G[16 (kw + WK g) + 4 q + t][lane % 16]; taps
     // outside the filter are outside the buffer and read zero
     float bop[NG][4];
@@ -356,7 +367,7 @@ __global__ __launch_bounds__(kMmThreads) void rsf_hetdec_mfma_k(HetdecArgs a, in
             float o = __shfl_xor(s, 4);  // the other part of the same output
             const bool im = l & 1;
             const int64_t j = b * NO + 128 * tile + 8 * (4 * (l >> 4) + v) + ((l & 15) >> 1);
-            if (__any(j < a.n_out && !(fabsf(s) <= 3.402823466e38f && fabsf(o) <= 3.402823466e38f))) {
+            if (__any(!(fabsf(s) <= 3.402823466e38f))) {
                 first = min(first, (int)(b - b0));
                 last = (int)(b - b0);
             }
@@ -368,24 +379,38 @@ __global__ __launch_bounds__(kMmThreads) void rsf_hetdec_mfma_k(HetdecArgs a, in
         }
     };
 
-    // this block's products into its wave's partial tile
+    // this block's products into its wave's partial tile.  Partial sum v < 16 has
+    // groups v, v + 16, ..: 16 / WK of them are this wave's, added here in the order
+    // of finish's tree
     auto multiply = [&](const float* w, float (*part)[256]) {
         const float* row = w + (16 * mt + J) * stride + 4 * q;
-        mm_v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0, acc2 = acc0, acc3 = acc0;
+        constexpr int U = kMmWaves / WK;
         // with padding 8 D is a multiple of 16, so a group of 16 taps lies in one chunk
+        auto partial = [&](int u) {
+            mm_v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0, acc2 = acc0, acc3 = acc0;
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            const unsigned kk = 16 * (kw + WK * g);
-            const float4 x = *reinterpret_cast<const float4*>(row + kk + pad * (int)(((uint64_t)kk * inv_chunk) >> 32));
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, bop[g][0], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, bop[g][1], acc1, 0, 0, 0);
-            acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, bop[g][2], acc2, 0, 0, 0);
-            acc3 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, bop[g][3], acc3, 0, 0, 0);
+            for (int g = u; g < NG; g += U) {
+                const unsigned kk = 16 * (kw + WK * g);
+                const float4 x = *reinterpret_cast<const float4*>(row + kk + pad * (int)(((uint64_t)kk * inv_chunk) >> 32));
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, bop[g][0], acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, bop[g][1], acc1, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, bop[g][2], acc2, 0, 0, 0);
+                acc3 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, bop[g][3], acc3, 0, 0, 0);
+            }
+            return (acc0 + acc1) + (acc2 + acc3);
+        };
+        mm_v4f sum = partial(0);
+        if constexpr (U == 2 && NG > 1) sum += partial(1);
+        if constexpr (U == 4) {
+            if constexpr (NG > 2) sum += partial(2);
+            if constexpr (NG > 1) {
+                mm_v4f odd = partial(1);
+                if constexpr (NG > 3) odd += partial(3);
+                sum += odd;
+            }
         }
         // D layout: lane holds rows 4 (lane / 16) + v, column lane % 16
-        *reinterpret_cast<float4*>(part[mt * WK + kw] + 4 * lane) =
-            make_float4((acc0[0] + acc1[0]) + (acc2[0] + acc3[0]), (acc0[1] + acc1[1]) + (acc2[1] + acc3[1]),
-                        (acc0[2] + acc1[2]) + (acc2[2] + acc3[2]), (acc0[3] + acc1[3]) + (acc2[3] + acc3[3]));
+        *reinterpret_cast<float4*>(part[mt * WK + kw] + 4 * lane) = make_float4(sum[0], sum[1], sum[2], sum[3]);
     };
 
     if constexpr (NB > 1) {
@@ -432,20 +457,29 @@ __global__ __launch_bounds__(kMmThreads) void rsf_hetdec_mfma_k(HetdecArgs a, in
 namespace {
 typedef void (*MmFn)(HetdecArgs, int, unsigned, bool, int64_t);
 
+template <int WK, int NG>
+MmFn mm_fn2() {
+    if constexpr (NG <= mm_groups_max(WK, 2))
+        return rsf_hetdec_mfma_k<WK, NG, 2>;
+    else
+        return nullptr;
+}
+
 template <int WK>
 MmFn mm_fn(int NG) {
     switch (NG) {
-        case 1: return rsf_hetdec_mfma_k<WK, 1, 2>;
-        case 2: return rsf_hetdec_mfma_k<WK, 2, 2>;
-        case 3: return rsf_hetdec_mfma_k<WK, 3, 2>;
-        case 4: return rsf_hetdec_mfma_k<WK, 4, 2>;
-        case 5: return rsf_hetdec_mfma_k<WK, 5, 2>;
-        case 6: return rsf_hetdec_mfma_k<WK, 6, 2>;
-        case 8: return rsf_hetdec_mfma_k<WK, 8, 2>;
-        case 10: return rsf_hetdec_mfma_k<WK, 10, 2>;
-        case 12: return rsf_hetdec_mfma_k<WK, 12, 2>;
-        case 14: return rsf_hetdec_mfma_k<WK, 14, 2>;
-        case 16: return rsf_hetdec_mfma_k<WK, 16, 2>;
+        case 1: return mm_fn2<WK, 1>();
+        case 2: return mm_fn2<WK, 2>();
+        case 3: return mm_fn2<WK, 3>();
+        case 4: return mm_fn2<WK, 4>();
+        case 5: return mm_fn2<WK, 5>();
+        case 6: return mm_fn2<WK, 6>();
+        case 7: return mm_fn2<WK, 7>();
+        case 8: return mm_fn2<WK, 8>();
+        case 10: return mm_fn2<WK, 10>();
+        case 12: return mm_fn2<WK, 12>();
+        case 14: return mm_fn2<WK, 14>();
+        case 16: return mm_fn2<WK, 16>();
         default: return nullptr;
     }
 }
@@ -478,7 +512,7 @@ hipError_t launch_hetdec(const HetdecArgs& a, int n_cu, hipStream_t s) {
         const int64_t no = 128 * (kMmWaves / m.WK);
         const int64_t n_blk = (a.n_out + no - 1) / no;
         const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n_blk, n_cu));
-        // windows start at samples 128 k D - K D
+        // a window starts at sample 128 k D - K D of the series, a row 8 D samples after another
         const bool wide = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && a.c % 4 == 0;
         // kk / (8 D) for kk < 2^16 by the reciprocal rounded up
         const unsigned inv = (unsigned)(((1ull << 32) + 8ull * a.D - 1) / (8ull * a.D));
