@@ -473,6 +473,8 @@ __global__ __launch_bounds__(kThreads, 4) void rsf_resample_run_k(ResampleArgs A
                     const float sp = sf * (1.0f / kPiF);
                     const float2 za = wz[hw - 1], zb = wz[hw];
                     zt = make_float2(sp * ax + (w0_ * za.x + w1_ * zb.x), sp * ay + (w0_ * za.y + w1_ * zb.y));
+                    // u on a sample: that one alone, also beside one that is not finite
+                    if (__builtin_expect(__any(sf == 0.f), 0) && sf == 0.f) zt = frac < 0.5f ? za : zb;
                 } else {
                     for (int i = 1; i <= W; ++i) {
                         const float w = tap_weight(A.ip, frac + (float)(hw - i), ((hw - i) & 1) ? -sf : sf, pin);
