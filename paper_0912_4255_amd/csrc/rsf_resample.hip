@@ -437,7 +437,9 @@ __global__ __launch_bounds__(kThreads, 4) void rsf_resample_run_k(ResampleArgs A
                 const float frac = (float)(u - fl);
                 const int base = (int)((int64_t)fl - hw + 1 - w0);
                 const double fn = floor(u + 0.5);
-                mk = v.gap != 1 && fn >= 0.0 && fn < (double)A.n;
+                // a position that is not a number (a sky that is not) is looked up as
+                // sample 0, as the general kernel does, and so reaches A', B', C'
+                mk = v.gap != 1 && !(fn < 0.0) && !(fn >= (double)A.n);
                 if (v.gap == 2) mk = mk && !in_gap(A.gaps, A.n_gaps, (int64_t)fn);
                 if (mk) {
                     sA += av * av;
