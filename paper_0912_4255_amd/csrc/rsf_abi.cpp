@@ -438,7 +438,7 @@ PointLayout point_layout(const rsf_plan* p, int64_t n_cand) {
 
 bool is_fin(double x) { return std::isfinite(x); }
 
-ResampleArgs base_resample_args(const rsf_plan* p, const rsf_segment* seg, int X) {
+ResampleArgs base_resample_args(const rsf_plan* p, const rsf_segment* seg, int X, bool api) {
     ResampleArgs a{};
     a.n = p->n;
     a.dt = p->d.dt;
@@ -450,7 +450,8 @@ ResampleArgs base_resample_args(const rsf_plan* p, const rsf_segment* seg, int X
     a.x = (const float2*)seg->x[X];
     a.gaps = seg->gaps[X];
     a.n_gaps = seg->n_gaps[X];
-    a.run = resample_interpolates(p->d.dt, p->eph) ? 1 : 0;
+    a.run = resample_interpolates(p->d.dt, p->eph, api) ? 1 : 0;
+    a.run_delay = resample_run_delay(api);
     return a;
 }
 
@@ -759,7 +760,7 @@ int rsf_resample(const rsf_plan* p, const rsf_segment* seg, const double* sky, i
     RSF_HIP(launch_fill_u32(flags, 16, 0u, s), "flags clear");
     const int64_t P = (p->n + kNaturalRow - 1) / kNaturalRow;
     for (int X = 0; X < p->d.n_det; ++X) {
-        ResampleArgs a = base_resample_args(p, seg, X);
+        ResampleArgs a = base_resample_args(p, seg, X, true);
         a.sky = sky;
         a.sky_stride = p->binary ? 5 : 2;
         a.binary = p->binary;
@@ -860,7 +861,7 @@ int run_fstat(const rsf_plan* p, const rsf_segment* seg, const double* sky, int6
         // steps 1-5 for the chunk's skies: the resampled series, A', B', C'
         auto resample_chunk = [&]() -> int {
             for (int X = 0; X < p->d.n_det; ++X) {
-                ResampleArgs a = base_resample_args(p, seg, X);
+                ResampleArgs a = base_resample_args(p, seg, X, false);
                 a.sky = sky + (p->binary ? 5 : 2) * c0;
                 a.sky_stride = p->binary ? 5 : 2;
                 a.binary = p->binary;

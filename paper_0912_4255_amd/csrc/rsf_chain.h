@@ -8,11 +8,11 @@
 // run and the interpolation window around it).  Each quantity is a sum of
 // circular motions, so with rate w and H = half dt the remainder is at most
 // A (w H)^5 / 1920, A the amplitude.  chain_interpolates() admits the sampling
-// intervals for which that is at most 1e-11 s for t_m and `beam` for a and b
+// intervals for which that is at most `delay` (s) for t_m and `beam` for a and b
 // (rate 2 w_sid; FP32 resolves 6e-8 of them, but the FP64 antenna sums of the
-// resampler show more), orbit_slow() the orbits for
-// which it is at most 1e-11 s for R and 3e-11 relative for its derivatives: at
-// 100 Hz and 1e-11 s the phase is off by 6e-9 rad.
+// resampler show more), orbit_slow() the orbits for which it is at most `delay` for
+// R (and 3e-11 relative for its derivatives).  What goes on in FP32 takes kDelayErr:
+// at 100 Hz and 1e-11 s the phase is off by 6e-9 rad.
 #pragma once
 
 #include <math.h>
@@ -23,15 +23,17 @@ namespace rsf {
 
 constexpr float kPiF = 3.14159265358979323846f;
 
+constexpr double kDelayErr = 1e-11;
+
 // H: half dt, in seconds
-inline bool chain_interpolates(const EphDev& e, double H, double beam) {
+inline bool chain_interpolates(const EphDev& e, double H, double delay, double beam) {
     const double xo = 2.0 * kPi * fabs(e.inv_p_orb) * H, xs = 2.0 * kPi * fabs(e.inv_p_sid) * H;
     auto p5 = [](double x) { return x * x * x * x * x / 1920.0; };
-    return fabs(e.au_c) * p5(xo) + fabs(e.re_c) * p5(xs) <= 1e-11 && p5(2.0 * xs) <= beam && xo <= 0.1;
+    return fabs(e.au_c) * p5(xo) + fabs(e.re_c) * p5(xs) <= delay && p5(2.0 * xs) <= beam && xo <= 0.1;
 }
-__device__ __forceinline__ bool orbit_slow(const BinaryOrbit& b, double H) {
+__device__ __forceinline__ bool orbit_slow(const BinaryOrbit& b, double H, double delay) {
     const double x = 2.0 * kPi / b.p_orb * H;
-    return x <= 0.035 && b.a_p * (x * x) * (x * x) * x <= 1e-11 * 1920.0;
+    return x <= 0.035 && b.a_p * (x * x) * (x * x) * x <= delay * 1920.0;
 }
 
 template <typename RUN>

@@ -12,7 +12,10 @@ namespace rsf {
 
 hipError_t launch_resample(const ResampleArgs& a, int n_sky, hipStream_t s);
 int resample_blocks(int LB, int64_t P);
-bool resample_interpolates(double dt, const EphDev& e);  // the interpolated timing chain holds at this sampling interval
+// the interpolated timing chain holds at this sampling interval (api: for FP64 outputs),
+// for orbits whose delay it gives to resample_run_delay (s)
+bool resample_interpolates(double dt, const EphDev& e, bool api);
+double resample_run_delay(bool api);
 hipError_t launch_antenna_reduce(const ReduceArgs& r, hipStream_t s);
 
 // The first pass's general-stage kernels of 128 and 256 threads

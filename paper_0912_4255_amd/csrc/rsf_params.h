@@ -119,6 +119,7 @@ struct ResampleArgs {
     int sky_stride;           // 2, or 5 with a binary orbit
     int binary;
     int run;                  // the interpolated timing chain takes the call (binary: the rows whose orbit it admits)
+    double run_delay;         // what it may be off by in an orbit's delay (s)
     // tile geometry: k = LB * n_a + n_b, 0 <= n_b < LB, 0 <= n_a < P
     int LB;
     int64_t P;

@@ -385,7 +385,7 @@ constexpr int kRunsMax = 8 * 4;  // runs of a workgroup
 constexpr int kRunWin = 416;
 
 __device__ __forceinline__ bool orbit_interpolates(const BinaryOrbit& b, double dt) {
-    return orbit_slow(b, PointRun::half * dt);
+    return orbit_slow(b, PointRun::half * dt, kDelayErr);
 }
 
 // Per run: quartics in s of the NQ quantities V = d / dt, a, b (and, for the
@@ -1257,7 +1257,7 @@ int point_rows(int64_t P) { return P <= 512 ? 1 : P <= 4096 ? 4 : P <= 8192 ? 8 
 int point_blocks(int64_t P, int rows) { return (int)((P + 4 * rows - 1) / (4 * rows)); }
 
 // sampling intervals up to 4.4 s
-bool point_interpolates(double dt, const EphDev& e) { return chain_interpolates(e, PointRun::half * dt, 4e-9); }
+bool point_interpolates(double dt, const EphDev& e) { return chain_interpolates(e, PointRun::half * dt, kDelayErr, 4e-9); }
 
 hipError_t launch_point(const PointArgs& a, bool grad, hipStream_t s) {
     const dim3 grid((unsigned)a.n_blocks, (unsigned)a.n_cand);

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(kThreads) void rsf_resample_k(ResampleArgs A) {
         const BinaryOrbit given{srow[2], srow[3], srow[4]};
         orbit_ok = orbit_admitted(given);
         bo = orbit_or_none(given);
-        if (A.run && orbit_ok && orbit_slow(bo, SeriesRun::half * A.dt)) return;
+        if (A.run && orbit_ok && orbit_slow(bo, SeriesRun::half * A.dt, A.run_delay)) return;
     }
     const double3 n0 = sky_unit(alpha, delta);
     const SkyFrame fr = sky_frame(alpha, delta);
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(kThreads, 4) void rsf_resample_run_k(ResampleArgs A
     BinaryOrbit bo{};
     if constexpr (BIN) {
         bo = BinaryOrbit{srow[2], srow[3], srow[4]};
-        if (!orbit_admitted(bo) || !orbit_slow(bo, SeriesRun::half * A.dt)) return;  // rsf_resample_k's
+        if (!orbit_admitted(bo) || !orbit_slow(bo, SeriesRun::half * A.dt, A.run_delay)) return;  // rsf_resample_k's
     }
     const int W = A.ip.taps, hw = W / 2;
     const float pin = kPiF / (float)A.ip.n;  // pi / n of the Dirichlet kernel
@@ -559,8 +559,17 @@ __global__ __launch_bounds__(256) void rsf_antenna_reduce_k(ReduceArgs R) {
     }
 }
 
-// sampling intervals up to 2.3 s: A', B', C' to 1e-11
-bool resample_interpolates(double dt, const EphDev& e) { return chain_interpolates(e, SeriesRun::half * dt, 1e-11); }
+// Into an FFT what is resampled goes in FP32: sampling intervals up to 2.3 s, with t_m to
+// kDelayErr and A', B', C' to 1e-11.  The API outputs t_m, u, A', B', C' are FP64, so there
+// the remainders stay below the exact chain's own error (the inversion's residual of up
+// to 1e-12 s): 3e-13 s and 1e-13, sampling intervals up to 0.95 s.  At the other rule's limits
+// t_m was off by 9.2e-12 s (a_p = 10 s, P_b = 4 h, dt = 0.5 s) against 6.3e-13 s for the
+// exact chain, A', B', C' by 5.7e-13 (dt = 2 s) against 6e-15.  Four binary rows of 864,001 samples:
+// 82 us interpolated, 227 us where the orbit is faster than that.
+double resample_run_delay(bool api) { return api ? 3e-13 : kDelayErr; }
+bool resample_interpolates(double dt, const EphDev& e, bool api) {
+    return chain_interpolates(e, SeriesRun::half * dt, resample_run_delay(api), api ? 1e-13 : 1e-11);
+}
 
 hipError_t launch_resample(const ResampleArgs& a, int n_sky, hipStream_t s) {
     const dim3 grid((unsigned)((a.LB + kTileB - 1) / kTileB), (unsigned)((a.P + kTileA - 1) / kTileA), (unsigned)n_sky);
