@@ -4,7 +4,7 @@
 // k = LB * n_a + n_b (16 runs of 128 consecutive samples).  Two kernels:
 // rsf_resample_run_k interpolates the timing chain along each run and carries
 // every ordinary call; rsf_resample_k evaluates it per sample (long sampling
-// intervals, fast or refused orbits), per run of 64 samples:
+// intervals, fast or refused orbits; orbits in half tiles), per run of 64 samples:
 //   1. every lane inverts eq. eq21 for its k in FP64 (one fixed-point step
 //      and one Newton step, residual below 1e-12 s);
 //   2. the wave loads the detector-grid window its 64 outputs need into LDS,
@@ -102,13 +102,15 @@ __device__ __forceinline__ void put_sample(const ResampleArgs& A, int sky, int64
 }
 
 // The tile to the FFT layout: element (n_b, n_a) at n_b P + n_a, 16 n_a at a time.
+template <int COLS>
 __device__ __forceinline__ void write_tile(const ResampleArgs& A, int sky, int b0, int64_t a0,
-                                           const float4 (&main)[kTileA][kTileB + 1], const float (&tm)[kTileA][kTileB + 1]) {
+                                           const float4 (&main)[kTileA][COLS + 1], const float (&tm)[kTileA][COLS + 1]) {
     if (A.layout != 1) return;
     const int64_t sky_off = (int64_t)sky * A.rs_sky_stride;
+    constexpr int threads = 4 * COLS;
 #pragma unroll
-    for (int q = 0; q < kTileA * kTileB / kThreads; ++q) {
-        const int e = threadIdx.x + q * kThreads;
+    for (int q = 0; q < kTileA * COLS / threads; ++q) {
+        const int e = threadIdx.x + q * threads;
         const int nb = e / kTileA, na = e % kTileA;
         if (b0 + nb < A.LB && a0 + na < A.P) {
             const int64_t idx = sky_off + (int64_t)(b0 + nb) * A.P + a0 + na;
@@ -118,9 +120,11 @@ __device__ __forceinline__ void write_tile(const ResampleArgs& A, int sky, int b
     }
 }
 
-// antenna-sum partials of the workgroup, fixed reduction order
-__device__ __forceinline__ void antenna_partials(const ResampleArgs& A, int sky, double sA, double sB, double sC,
-                                                 double (&red)[kWaves][3]) {
+// antenna-sum partials of the workgroup, fixed reduction order, to (or, ADD, into)
+// the sums of tile `tile` of a row of tiles
+template <bool ADD, int WAVES>
+__device__ __forceinline__ void antenna_partials(const ResampleArgs& A, int sky, int tile, int row_tiles, double sA,
+                                                 double sB, double sC, double (&red)[WAVES][3]) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         sA += __shfl_xor(sA, off);
@@ -137,8 +141,12 @@ __device__ __forceinline__ void antenna_partials(const ResampleArgs& A, int sky,
     if (threadIdx.x < 3) {
         double t = 0.0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) t += red[w][threadIdx.x];
-        A.partials[((int64_t)sky * A.n_blocks + blockIdx.y * gridDim.x + blockIdx.x) * 3 + threadIdx.x] = t;
+        for (int w = 0; w < WAVES; ++w) t += red[w][threadIdx.x];
+        double* p = A.partials + ((int64_t)sky * A.n_blocks + blockIdx.y * row_tiles + tile) * 3 + threadIdx.x;
+        if (ADD)
+            atomicAdd(p, t);
+        else
+            *p = t;
     }
 }
 }  // namespace
@@ -147,15 +155,21 @@ __device__ __forceinline__ void antenna_partials(const ResampleArgs& A, int sky,
 // emission time (target t_b + R(t_s + t_b) of the inversion) and the delay
 // used by the correction and stored for the spindown phase is the total
 // d = t_m - R(tau_e), tau_e from tau_e + R(tau_e) = tau + t_m(tau).
-template <bool BIN>
-__global__ __launch_bounds__(kThreads) void rsf_resample_k(ResampleArgs A) {
+// COLS: 128, or 64 with orbits: half tiles in workgroups of 4 waves, of which a CU
+// holds three where it holds one of 8 (161 registers), adding their antenna sums
+// into the tile's, which rsf_resample_run_k<true> or the launch clears: two numbers
+// added to 0, the same in either order.  Four rows of 864,001 samples with an orbit of
+// one hour: 270 us, 302 us in whole tiles; one of 86,400: 40 and 48 us.
+template <bool BIN, int COLS>
+__global__ __launch_bounds__(4 * COLS) void rsf_resample_k(ResampleArgs A) {
+    constexpr int kWaves = COLS / 16, kHalves = COLS / 64;
     __shared__ float2 win[kWaves][kWinMax];
-    __shared__ float4 tile_main[kTileA][kTileB + 1];
-    __shared__ float tile_tm[kTileA][kTileB + 1];
+    __shared__ float4 tile_main[kTileA][COLS + 1];
+    __shared__ float tile_tm[kTileA][COLS + 1];
     __shared__ double red[kWaves][3];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int b0 = blockIdx.x * kTileB;
+    const int b0 = blockIdx.x * COLS;
     const int64_t a0 = (int64_t)blockIdx.y * kTileA;
     const int sky = blockIdx.z;
     const double* srow = A.sky + (int64_t)A.sky_stride * sky;
@@ -179,8 +193,8 @@ __global__ __launch_bounds__(kThreads) void rsf_resample_k(ResampleArgs A) {
     const bool flat = A.ip.kernel == 1 && pin * (float)(hw + 1) < 2.9e-4f;
     double sA = 0.0, sB = 0.0, sC = 0.0;
     bool window_overflow = false;
-    for (int unit = wave; unit < 2 * kTileA; unit += kWaves) {
-        const int ia = unit >> 1, ib = (unit & 1) * 64 + lane;
+    for (int unit = wave; unit < kHalves * kTileA; unit += kWaves) {
+        const int ia = unit >> (kHalves - 1), ib = (unit & (kHalves - 1)) * 64 + lane;
         const int64_t n_a = a0 + ia;
         const int n_b = b0 + ib;
         const int64_t k = (int64_t)A.LB * n_a + n_b;
@@ -295,8 +309,11 @@ __global__ __launch_bounds__(kThreads) void rsf_resample_k(ResampleArgs A) {
 
     if (window_overflow && lane == 0) atomicOr(A.flags, 2u);
     if (!orbit_ok && threadIdx.x == 0) atomicOr(A.flags, 4u);
-    write_tile(A, sky, b0, a0, tile_main, tile_tm);
-    antenna_partials(A, sky, sA, sB, sC, red);
+    write_tile<COLS>(A, sky, b0, a0, tile_main, tile_tm);
+    if constexpr (COLS == kTileB)
+        antenna_partials<false>(A, sky, blockIdx.x, gridDim.x, sA, sB, sC, red);
+    else
+        antenna_partials<true>(A, sky, blockIdx.x / 2, (gridDim.x + 1) / 2, sA, sB, sC, red);
 }
 
 // The interpolated chain: the tile's 16 runs of 128 samples, two per wave.  The
@@ -330,7 +347,10 @@ __global__ __launch_bounds__(kThreads, 4) void rsf_resample_run_k(ResampleArgs A
     BinaryOrbit bo{};
     if constexpr (BIN) {
         bo = BinaryOrbit{srow[2], srow[3], srow[4]};
-        if (!orbit_admitted(bo) || !orbit_slow(bo, SeriesRun::half * A.dt, A.run_delay)) return;  // rsf_resample_k's
+        if (!orbit_admitted(bo) || !orbit_slow(bo, SeriesRun::half * A.dt, A.run_delay)) {  // rsf_resample_k's
+            if (tid < 3) A.partials[((int64_t)sky * A.n_blocks + blockIdx.y * gridDim.x + blockIdx.x) * 3 + tid] = 0.0;
+            return;
+        }
     }
     const int W = A.ip.taps, hw = W / 2;
     const float pin = kPiF / (float)A.ip.n;  // pi / n of the Dirichlet kernel
@@ -492,8 +512,8 @@ __global__ __launch_bounds__(kThreads, 4) void rsf_resample_run_k(ResampleArgs A
     }
     __syncthreads();  // the tile rows of all waves are complete
     if (__any(overflow) && lane == 0) atomicOr(A.flags, 2u);
-    write_tile(A, sky, b0, a0, tile_main, tile_tm);
-    antenna_partials(A, sky, sA, sB, sC, red);
+    write_tile<kTileB>(A, sky, b0, a0, tile_main, tile_tm);
+    antenna_partials<false>(A, sky, blockIdx.x, gridDim.x, sA, sB, sC, red);
 }
 
 // One workgroup per sky: sums the block partials of every detector in a
@@ -581,11 +601,18 @@ hipError_t launch_resample(const ResampleArgs& a, int n_sky, hipStream_t s) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || !a.binary) return e;
     }
-    // a binary plan's sky rows choose their kernel on the device, by their orbit
-    if (a.binary)
-        hipLaunchKernelGGL(rsf_resample_k<true>, grid, dim3(kThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL(rsf_resample_k<false>, grid, dim3(kThreads), 0, s, a);
+    if (!a.binary) {
+        hipLaunchKernelGGL((rsf_resample_k<false, kTileB>), grid, dim3(kThreads), 0, s, a);
+        return hipGetLastError();
+    }
+    // a binary plan's sky rows choose their kernel on the device, by their orbit;
+    // the half tiles' antenna sums are added into cleared ones
+    const dim3 halves((unsigned)((a.LB + 63) / 64), grid.y, grid.z);
+    if (!a.run) {
+        const hipError_t e = launch_fill_u32((unsigned int*)a.partials, 6 * a.n_blocks * n_sky, 0u, s);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((rsf_resample_k<true, 64>), halves, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
