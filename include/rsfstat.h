@@ -24,6 +24,25 @@
  * - 2F = 2 (B'|f_a|^2 + A'|f_b|^2 - 2 C' Re(f_a f_b^*)) / D' with
  *   noise-weighted sums (weights 1/sigma_X^2) over detectors (eq. eq6).
  *
+ * Precision
+ * ---------
+ * FP32 bulk (series, interpolation weights, phases reduced mod 1 in FP64, FFTs),
+ * FP64 timing, antenna sums and partial sums.  The timing chain (T^k, t_m, a, b and
+ * their derivatives; with a binary orbit the total delay) is evaluated in FP64 at five
+ * samples of a run and carried to its other samples by quartics in FP64 where
+ * their remainder is bounded by what follows, else at every sample:
+ * - searches (rsf_fstat, _topk, _segments, _semicoherent; runs of 128 samples): 1e-11 s
+ *   in t_m and in an orbit's delay and 1e-11 in a, b, that is sampling intervals up
+ *   to 2.3 s with the Earth's motion, and orbits with (2 pi / P_b) 82 dt <= 0.035 and
+ *   a_p (2 pi / P_b)^5 (82 dt)^5 / 1920 <= 1e-11 s;
+ * - rsf_fstat_point and _backward (256 samples): 1e-11 s, and 4e-9 in a, b, up to 4.4 s;
+ *   orbits as above with 146 dt;
+ * - rsf_resample, whose t_m, u, A', B', C' are FP64 outputs: 3e-13 s and 1e-13, up to
+ *   0.95 s (the evaluation at every sample leaves a residual of up to 1e-12 s and the
+ *   rounding of T).
+ * The bounds do not depend on f_het: 1e-11 s is 2e-8 cycles at 2 kHz, below the
+ * FP32 step of a phase.
+ *
  * Memory and streams
  * ------------------
  * Every array argument is caller-owned DEVICE memory unless marked "host".
@@ -40,8 +59,9 @@
  * Nothing aborts or throws across this interface.  A template whose Gram
  * determinant D' is not positive (e.g. an all-gap segment) yields NaN outputs
  * and sets RSF_FLAG_DEGENERATE in the flags word readable with rsf_get_flags.
- * A run of 64 consecutive resampled times whose interpolation windows span
- * more detector samples than a wave stages (only for time compressions far
+ * A run of 64 consecutive resampled times (of 128 or 256 where the timing chain is
+ * interpolated) whose interpolation windows span more detector samples than a
+ * wave stages (104 - taps per 64, only for time compressions far
  * beyond any physical Doppler factor) yields NaN samples there and sets
  * RSF_FLAG_WINDOW.  A binary orbit outside the admitted range (see
  * rsf_plan_set_binary) makes the kernels that read it set RSF_FLAG_ORBIT and
