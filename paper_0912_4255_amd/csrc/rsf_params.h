@@ -62,8 +62,10 @@ struct FftStages {
 // 5488 (over the limit at 256).  `least`: rows of up to kRowsPerDevice columns
 // (one row per CU for a lone template, whose time is a row's) keep 256: 13.3 us
 // against 15.7 at 128 and 13.9 at 512 for 1350 x 256 points, and 175 against 138
-// and 289 us for 64 templates of them.  Nothing here depends on the launch, so
-// every batching computes the same bits.
+// and 289 us for 64 templates of them.  Nothing here depends on the launch or on
+// how the device is partitioned (kRowsPerDevice is the whole card's 256 CUs), so
+// every batching computes the same bits: the thread count is the stride of the
+// inter-pass twiddles' recurrence.
 constexpr int kRowPointsPlan = 17, kRowPointsGeneral = 13, kRowsPerDevice = 256;
 constexpr int row_threads(const int* radix, int n_stages, int len, int most, int least = 128) {
     int best = kFftThreads;
