@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kHdThreads) void rsf_hetdec_k(HetdecArgs a) {
 // for the samples alone (5 TB/s), about 400 us for both together; the product
 // form for D = 64 alone that this replaces (rows of 64 samples, one output tap
 // phase per column, a diagonal sum through LDS) took 404 us.  One day at 1 kHz,
-// D = 100, K = 16: 177 us against 1530 us for the direct sum.  Vector
+// D = 100, K = 16: 175 us against 1530 us for the direct sum.  Vector
 // instructions hold up FP32 products: with the samples staged through registers
 // (237 vector instructions per wave and block, 17 of them products) the D = 64
 // case took 546 us.  A third window buffer changed nothing.
